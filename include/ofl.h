@@ -189,8 +189,13 @@ int ofl_get_regions(const ofl_grid *g, unsigned *mask, int level[3], int *xfer_m
  * a data region is open (ofl_data_enter), in which case p stays on the device
  * until ofl_update_host/ofl_data_exit. *gosa_out (nullable) receives R of the
  * last iteration, i.e. the residual of the iterate before the last update;
- * iters == 0 leaves p alone and gives NaN. EINVAL for iters < 0 or omega == 0
- * or non-finite; EDEVICE when a GPU nest is requested and no GPU is usable. */
+ * iters == 0 leaves p alone and gives NaN. With every nest on the GPU as one
+ * region, hoisted transfers, no tile set or searched, profiling off and outside
+ * a batch, the iterations before the last run two per launch (one pass over the
+ * read-only arrays serves both; p is bitwise the same, and so is gosa, which the
+ * last iteration computes by itself; wrk2's device content after such a run is
+ * unspecified, as after a fused one). EINVAL for iters < 0 or omega == 0 or
+ * non-finite; EDEVICE when a GPU nest is requested and no GPU is usable. */
 int ofl_jacobi_run(ofl_grid *g, int iters, float omega, double *gosa_out);
 
 /* ofl_jacobi_run for callers that cannot allocate device memory (code under

@@ -636,6 +636,7 @@ namespace {
 // only (no memset or copy nodes). A graph is reused while the grid's view,
 // tile, omega and length are those it was captured with.
 constexpr int kGraphIters = 256;
+constexpr double kPairGraphPoints = 8e6;
 
 bool same_view(const GridView &a, const GridView &b) {
     for (int n = 0; n < kNCoef; ++n)
@@ -649,6 +650,48 @@ bool same_view(const GridView &a, const GridView &b) {
 bool same_tile(const TileCfg &a, const TileCfg &b) {
     return a.vec == b.vec && a.rows == b.rows && a.kchunk == b.kchunk && a.flags == b.flags &&
            a.occupancy == b.occupancy;
+}
+
+// ---- iterations in pairs
+//
+// With every nest on the GPU as one region and hoisted transfers, nothing reads
+// what an iteration other than the last leaves behind, except the next one. The
+// pair sweep (pair.hip) runs two of them in one launch, residuals included, with
+// p and wrk2 exchanged instead of copied; p is bitwise what the nests give. The
+// last iteration of a run always goes nest by nest (or as the fused sweep), so
+// gosa is summed as ever, and an odd one runs first.
+//
+// A tile the caller chose or searched, profiling and a time limit (which look
+// at single nests) and grids inside a batch (whose tables hold the buffers)
+// keep single iterations.
+bool pair_eligible(ofl_grid *g, int iters) {
+    if (launch_pair == nullptr || iters < 3 || g->mask != OFL_MASK_ALL_GPU || g->mode != OFL_XFER_HOISTED ||
+        g->profiling || g->deadline_ns != 0 || g->batch_refs != 0 || g->tile_chosen || !grid_whole_nests(g))
+        return false;
+    if (!g->pair_planned) {
+        const int pitch = round_up(g->I, g->row_align > 0 ? g->row_align : kPitchAlign);
+        if (!pair_plan(g->I, g->J, g->K, pitch, g->fmt == OFL_COEF_F32 ? 4 : 2, &g->pair))
+            g->pair.vec = 0;
+        g->pair_planned = true;
+    }
+    return g->pair.vec != 0;
+}
+
+// Pairs and their last sums on the grid's stream. The partials (two buffers of
+// two sums per work-group) live in the transfer staging buffer, which is idle
+// between transfers and ordered with them by the stream; pair_plan keeps to what
+// it holds.
+void enqueue_pairs(ofl_grid *g, int pairs, float omega) {
+    const PairShape &shape = g->pair;
+    double *parts = reinterpret_cast<double *>(g->block + g->lay.staging_off);
+    const long long half = 2LL * shape.blocks();
+    GridView v = g->view;
+    for (int t = 0; t < pairs; ++t) {
+        launch_pair(v, g->fmt != OFL_COEF_F32, shape, omega, parts + (t & 1) * half,
+                    t > 0 ? parts + ((t - 1) & 1) * half : nullptr, g->stream);
+        std::swap(v.p, v.wrk2);
+    }
+    launch_pair_fold(parts + ((pairs - 1) & 1) * half, shape, omega, v.gosa, g->stream);
 }
 
 bool graph_eligible(const ofl_grid *g, int nests) {
@@ -665,11 +708,12 @@ void enqueue_iterations(ofl_grid *g, int iters, float omega) {
 }
 
 // A graph of `iters` steady-state iterations, cached; nullptr when the stream
-// cannot be captured (for instance because the caller is capturing it).
-hipGraphExec_t loop_graph(ofl_grid *g, int iters, float omega) {
+// cannot be captured (for instance because the caller is capturing it). With
+// `pairs` they run in pairs (their shape follows from the grid).
+hipGraphExec_t loop_graph(ofl_grid *g, int iters, float omega, bool pairs = false) {
     for (const auto &c : g->graphs)
         if (c.exec && c.iters == iters && c.omega == omega && c.whole_rows == g->wrk2_boundary_ok &&
-            same_tile(c.tile, g->tile) && same_view(c.view, g->view))
+            c.pairs == pairs && same_tile(c.tile, g->tile) && same_view(c.view, g->view))
             return c.exec;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(g->stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
@@ -685,7 +729,10 @@ hipGraphExec_t loop_graph(ofl_grid *g, int iters, float omega) {
     hipGraph_t graph = nullptr;
     hip_check(hipStreamBeginCapture(g->stream, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
     try {
-        enqueue_iterations(g, iters, omega);
+        if (pairs)
+            enqueue_pairs(g, iters / 2, omega);
+        else
+            enqueue_iterations(g, iters, omega);
     } catch (...) {
         (void)hipStreamEndCapture(g->stream, &graph);
         if (graph)
@@ -703,6 +750,7 @@ hipGraphExec_t loop_graph(ofl_grid *g, int iters, float omega) {
     slot.omega = omega;
     slot.iters = iters;
     slot.whole_rows = g->wrk2_boundary_ok;
+    slot.pairs = pairs;
     return exec;
 }
 
@@ -752,7 +800,68 @@ void grid_drop_graphs(ofl_grid *g) {
         }
 }
 
+namespace {
+
+// Iterations [from, from + 2 * pairs) in pairs. Unfused runs of grids that are
+// bound by their launches replay them from a graph; fused runs launch them (the
+// entry point that allocates nothing creates no graphs).
+void run_pairs(ofl_grid *g, int from, int pairs, float omega) {
+    grid_ensure_device(g);
+    std::vector<Xfer> xs;
+    plan_before(from, kS, true, OFL_XFER_HOISTED, g->valid, xs);
+    grid_exec(g, xs);
+    xs.clear();
+    grid_sync_wrk2_boundary(g);
+    const bool graphed = g->fusion == 0 && static_cast<double>(g->n) <= kPairGraphPoints;
+    for (int done = 0; done < pairs;) {
+        const int n = std::min(pairs - done, kGraphIters / 2);
+        hipGraphExec_t exec = graphed ? loop_graph(g, 2 * n, omega, true) : nullptr;
+        if (exec) {
+            TraceRange range("ofl:graph of iterations");
+            hip_check(hipGraphLaunch(exec, g->stream), "hipGraphLaunch");
+        } else {
+            TraceRange range("ofl:iterations in pairs");
+            enqueue_pairs(g, n, omega);
+        }
+        if (n & 1)
+            grid_swap_p_wrk2(g);
+        done += n;
+    }
+    for (int nest = 0; nest < 3; ++nest) {
+        plan_after(from, nest, true, OFL_XFER_HOISTED, g->valid, xs);
+        g->stats.gpu_nests[nest] += static_cast<uint64_t>(2 * pairs);
+        if (g->fusion == 0)
+            g->stats.gpu_regions[nest] += static_cast<uint64_t>(2 * pairs);
+    }
+    g->gosa_on_dev = true;
+    g->pending = true;
+}
+
+// The iterations of a run that go in pairs, after an odd one: returns how many
+// iterations ran (0: none of it applies).
+template <class Single>
+int run_in_pairs(ofl_grid *g, int iters, float omega, Single &&single) {
+    if (!pair_eligible(g, iters))
+        return 0;
+    const int odd = (iters - 1) & 1;
+    if (odd)
+        single(1);
+    run_pairs(g, odd, (iters - 1 - odd) / 2, omega);
+    return iters - 1;
+}
+
+void run_single_iterations(ofl_grid *g, int iters, float omega, int nests);
+
+}  // namespace
+
 void grid_run_loop(ofl_grid *g, int iters, float omega, int nests) {
+    auto single = [&](int n) { run_single_iterations(g, n, omega, nests); };
+    single(iters - (nests == 3 ? run_in_pairs(g, iters, omega, single) : 0));
+}
+
+namespace {
+
+void run_single_iterations(ofl_grid *g, int iters, float omega, int nests) {
     if (nests == 3 && g->fusion != 0 && g->mask == OFL_MASK_ALL_GPU && g->mode == OFL_XFER_HOISTED &&
         g->batch_refs == 0 && grid_whole_nests(g)) {
         run_fused(g, iters, omega);
@@ -836,6 +945,8 @@ void grid_run_loop(ofl_grid *g, int iters, float omega, int nests) {
         }
     }
 }
+
+}  // namespace
 
 double grid_fetch_gosa(ofl_grid *g) {
     if (g->gosa_on_dev) {
@@ -1193,7 +1304,9 @@ int ofl_jacobi_run_static(ofl_grid *g, int iters, float omega, double *gosa_out)
             return;
         }
         grid_ensure_device(g);  // device state exists: selects the grid's device only
-        run_fused(g, iters, omega, static_scratch(g->device));
+        double *scratch = static_scratch(g->device);
+        auto single = [&](int n) { run_fused(g, n, omega, scratch); };
+        single(iters - run_in_pairs(g, iters, omega, single));
         const double gosa = grid_fetch_gosa(g);
         if (gosa_out)
             *gosa_out = gosa;

@@ -9,6 +9,7 @@
 
 #include "abi_util.hpp"
 #include "ofl_internal.hpp"
+#include "pair.hpp"
 #include "planner.hpp"
 
 struct ofl_grid {
@@ -83,8 +84,11 @@ struct ofl_grid {
         float omega = 0.f;
         int iters = 0;
         bool whole_rows = false;
+        bool pairs = false;  // iterations in pairs (pair.hip)
     };
     LoopGraph graphs[2];
+    ofl::PairShape pair;        // decomposition of iterations in pairs (vec 0: none)
+    bool pair_planned = false;
     int graph_next = 0;  // slot the next capture replaces
 
     bool broken = false;

@@ -1,0 +1,107 @@
+// The pair sweep (pair.hip): two iterations in one pass over the coefficients,
+// and the rule that decides where and in what decomposition it runs.
+#pragma once
+
+#include <algorithm>
+
+#include "ofl_internal.hpp"
+
+namespace ofl {
+
+// Points at either end of a tile inside a row that it computes for its own
+// second step only: two, in whole lanes.
+__host__ __device__ inline constexpr int pair_margin(int vec) { return vec < 2 ? 2 : vec; }
+
+// Decomposition of one grid's pair sweep: tiles of 64*vec points along i (which
+// overlap by two margins), waves-2 rows along j and `chunk` planes along k.
+struct PairShape {
+    int vec = 0, waves = 0;
+    int nti = 0, njt = 0, nkc = 0, chunk = 0;
+    int blocks() const { return nti * njt * nkc; }
+};
+
+inline int pair_itiles(int I, int vec) {
+    const int span = kWave * vec, stride = span - 2 * pair_margin(vec);
+    return I - 1 <= span ? 1 : 1 + (I - 1 - span + stride - 1) / stride;
+}
+
+// The decomposition a grid's iterations run in pairs with; false where they run
+// one by one.
+//
+// A launch is a few rounds of resident work-groups (one per CU at 4 points per
+// lane, whose registers fill it, two below). A round costs chunk + 3 planes (two
+// margin planes, and the fill of the pipeline), a plane a fixed part (its
+// barrier and arithmetic) and its share of the memory rate, both fitted to
+// launches of 12 grids from 33x33x65 to 385x257x385 in 30 to 60 decompositions
+// each; what the last-level cache holds (arrays of up to 224 MiB) streams twice
+// as fast. The choice is within 3% of the best measured one on 20 of the 24
+// grids and formats, 10% at worst. What it decides most is how full the last
+// round is: at 257x257x513 in FP32, 7 waves and 5 chunks make 255 work-groups
+// of one round (371 us), 8 waves 258 of two (603 us) or 473 (394 us).
+//
+// A work-group computes rows and planes beyond its own for its second step. A
+// large grid runs in pairs only where that is at most 2.2 times its points (a
+// slab of a few rows would spend more on them than the pair saves); a small
+// one, bound by its launches, always does: 33x33x65 14.0 -> 3.1 us per
+// iteration.
+inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *best) {
+    if (static_cast<long long>(pitch) * J > (1LL << 28))
+        return false;  // offsets inside a plane are 32-bit byte counts
+    const double points = static_cast<double>(I) * J * K;
+    const double bytes = points * (12 * coef_elem + 8);
+    const double per_row = (coef_elem == 4 ? 1.0e-4 : 0.52e-4) * (bytes < 224.0 * (1 << 20) ? 1.0 : 2.0);
+    // points per lane, waves, us per plane besides its loads
+    constexpr struct {
+        int vec, waves;
+        double fixed;
+    } kForms[] = {{4, 8, 1.54}, {4, 7, 1.39}, {2, 8, 1.23}, {1, 8, 0.74}};
+    double best_us = 0.0;
+    best->vec = 0;
+    for (const auto &form : kForms) {
+        if (form.vec == 1 && I - 1 > kWave)
+            continue;  // tiles of 60 points split cache lines
+        PairShape s;
+        s.vec = form.vec;
+        s.waves = form.waves;
+        s.nti = pair_itiles(I, s.vec);
+        s.njt = (J - 2 + s.waves - 3) / (s.waves - 2);
+        const long long slots = 256 * (s.vec == 4 ? 1 : 2);
+        const long long tiles = static_cast<long long>(s.nti) * s.njt;
+        // rows of 64 points that a work-group loads per plane (80 more points
+        // for a tile boundary: the overlap and the lines it splits)
+        const double rows = s.waves * (I + 80.0 * (s.nti - 1)) / s.nti / kWave;
+        for (int nkc = 1; nkc <= std::min(K - 2, 1024) && tiles * nkc <= 8192; ++nkc) {
+            const int chunk = (K - 2 + nkc - 1) / nkc;
+            if (chunk == s.chunk)
+                continue;
+            s.chunk = chunk;
+            s.nkc = (K - 2 + chunk - 1) / chunk;
+            // the partial sums live in the grid's staging buffer
+            if (32.0 * s.blocks() > 4.0 * points)
+                continue;
+            const double work = static_cast<double>(s.blocks()) * s.waves * (chunk + 2);
+            if (bytes > 16e6 && work > 2.2 * s.nti * (J - 2.0) * (K - 2.0))
+                continue;
+            double us = 3.0 + 0.004 * s.blocks();
+            for (long long left = s.blocks(); left > 0; left -= slots)
+                us += (chunk + 3) * (form.fixed + std::min(left, slots) * rows * per_row);
+            if (best->vec == 0 || us < best_us) {
+                best_us = us;
+                *best = s;
+            }
+        }
+    }
+    return best->vec != 0;
+}
+
+// parts: 2 * blocks() doubles, every one written; prev: the previous pair's
+// parts (same shape), whose two residuals this launch turns into gosa, or null.
+// Weak: the host code also links without the device code (it then runs every
+// iteration by itself).
+__attribute__((weak)) void launch_pair(const GridView &g, int bf16, const PairShape &s, float omega, double *parts,
+                                       const double *prev, hipStream_t st);
+// The last pair's two residuals into gosa.
+__attribute__((weak)) void launch_pair_fold(const double *parts, const PairShape &s, float omega, double *gosa,
+                                            hipStream_t st);
+
+}  // namespace ofl

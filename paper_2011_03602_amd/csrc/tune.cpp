@@ -832,8 +832,10 @@ int ofl_grid_tune(ofl_grid *g, const ofl_ga_params *ga_in, ofl_tune_result *out)
         const unsigned mask = g->mask;
         const int mode = g->mode;
         const TileCfg old = g->tile;
+        const bool chosen = g->tile_chosen;
         g->mask = OFL_MASK_ALL_GPU;
         g->mode = OFL_XFER_HOISTED;
+        g->tile_chosen = true;  // the runs measure the tile: no iterations in pairs
         std::map<uint32_t, bool> checked;
         auto evaluate = [&](uint32_t gene) -> double {
             TileCfg t;
@@ -856,6 +858,7 @@ int ofl_grid_tune(ofl_grid *g, const ofl_ga_params *ga_in, ofl_tune_result *out)
             g->mask = mask;
             g->mode = mode;
             g->tile = old;
+            g->tile_chosen = chosen;
             throw;
         }
         grid_sync(g);

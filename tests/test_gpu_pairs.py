@@ -1,0 +1,99 @@
+"""Iterations in pairs (the pair sweep) against the same iterations nest by nest.
+
+A run of three iterations or more with every nest on the GPU, hoisted transfers
+and no tile of its own goes two iterations per launch; profiling keeps it nest
+by nest. Both give every point the same operations in the same order and end on
+the same single iteration, so p must be bitwise equal and gosa exactly equal."""
+
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2011_03602_amd as ofl
+import synth
+from helpers import OMEGA, TOL_GOSA_F32, TOL_P_F32, boundary_equal, p_rel_err
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # collected on CPU hosts, skipped there
+    pytestmark = [pytest.mark.gpu, pytest.mark.skip(reason="needs a GPU")]
+
+FUSE_ALL = ofl.OFL_FUSE_RESIDUAL | ofl.OFL_FUSE_COPYBACK_SWAP
+
+
+def say(*args):
+    print("[gpu]", *args, flush=True)
+    sys.stdout.flush()
+
+
+def run(a, fmt, iters_list, profiled, fusion=0, sum_mode=ofl.OFL_SUM_F64, row_align=0):
+    g = ofl.Grid(a, coef_format=fmt, sum_mode=sum_mode, row_align=row_align)
+    ofl.ofl_set_fusion(g.handle, fusion)
+    ofl.ofl_set_profiling(g.handle, profiled)
+    ofl.ofl_data_enter(g.handle)
+    gosa = [ofl.ofl_jacobi_run(g.handle, n, OMEGA) for n in iters_list]
+    ofl.ofl_data_exit(g.handle)
+    assert list(ofl.ofl_get_stats(g.handle).gpu_nests) == [sum(iters_list)] * 3
+    p = g.p.copy()
+    g.close()
+    return p, gosa
+
+
+# Rows that end at, before and past a tile of 64, 128 and 256 points (the
+# boundary column inside the tile, just past it, a second and third tile), rows
+# and planes around a work-group's 5 or 6 rows and its chunk, the smallest grid.
+SHAPES = [(3, 3, 3), (4, 9, 5), (64, 8, 7), (65, 7, 12), (66, 15, 6), (129, 14, 9), (130, 13, 8), (256, 8, 5),
+          (257, 12, 21), (258, 9, 33), (505, 8, 6), (506, 9, 4), (770, 7, 5), (97, 41, 30)]
+
+
+@pytest.mark.parametrize("fmt", [ofl.OFL_COEF_F32, ofl.OFL_COEF_BF16, ofl.OFL_COEF_BF16_OFFSET])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_pairs_equal_single_iterations(shape, fmt):
+    say("pairs", shape, "format", fmt)
+    a = synth.make_problem(*shape, seed=synth.grid_seed(sum(shape)))
+    for row_align in (0, 4):
+        iters = [3, 6, 4]  # none, then an odd and an even number of pairs behind a single iteration
+        p1, g1 = run(a, fmt, iters, True, row_align=row_align)
+        p2, g2 = run(a, fmt, iters, False, row_align=row_align)
+        assert np.array_equal(p1, p2)
+        assert g1 == g2
+    if fmt == ofl.OFL_COEF_F32:
+        p_o, g_o = oracle.jacobi(a, sum(iters), float(OMEGA))
+        # a converged point's term is FP32 rounding: below (2 ulp of a value of at most 2)^2
+        floor = p_o.size * (2 * 2.0 ** -22 / float(OMEGA)) ** 2
+        assert p_rel_err(p2, p_o) <= TOL_P_F32 and abs(g2[-1] - g_o) <= TOL_GOSA_F32 * g_o + floor
+    assert boundary_equal(p2, a["p"])
+
+
+@pytest.mark.parametrize("fusion,sum_mode", [(ofl.OFL_FUSE_RESIDUAL, ofl.OFL_SUM_F64),
+                                             (ofl.OFL_FUSE_COPYBACK_SWAP, ofl.OFL_SUM_KAHAN_F32),
+                                             (FUSE_ALL, ofl.OFL_SUM_F64), (0, ofl.OFL_SUM_KAHAN_F32)])
+def test_pairs_in_every_form(fusion, sum_mode):
+    say("pairs, fusion", fusion, "sum", sum_mode)
+    a = synth.make_problem(131, 37, 45, seed=5)
+    for iters in ([5], [6, 3], [4, 4]):
+        p1, g1 = run(a, ofl.OFL_COEF_F32, iters, True, fusion, sum_mode)
+        p2, g2 = run(a, ofl.OFL_COEF_F32, iters, False, fusion, sum_mode)
+        assert np.array_equal(p1, p2)
+        assert g1 == g2
+
+
+def test_pairs_replay_and_continue():
+    """Pairs replayed from graphs, with the program's own work between the
+    replays, long enough for several graphs, and a change of omega."""
+    say("pairs, replays")
+    a = synth.make_problem(41, 23, 37, seed=6)
+    one, two = ofl.Grid(a), ofl.Grid(a)
+    ofl.ofl_set_profiling(one.handle, True)
+    for iters, om in [(8, OMEGA), (8, OMEGA), (8, OMEGA), (300, OMEGA), (8, np.float32(0.7)), (5, OMEGA), (8, OMEGA)]:
+        x1 = ofl.ofl_jacobi_run(one.handle, iters, om)
+        x2 = ofl.ofl_jacobi_run(two.handle, iters, om)
+        torch.ones(1000, device="cuda").sum().item()
+        assert x1 == x2
+        assert np.array_equal(one.p, two.p)
+    assert ofl.ofl_residual(one.handle) == ofl.ofl_residual(two.handle)
+    one.close()
+    two.close()
