@@ -49,6 +49,10 @@ void free_tables(ofl_batch *b) {
     free_dev(b->d_ritems);
     free_dev(b->d_range);
     free_dev(b->d_partials);
+    free_dev(b->d_pitems);
+    free_dev(b->d_prange);
+    free_dev(b->d_pparts);
+    b->p_cnt = 0;
     b->tables_ready = false;
 }
 
@@ -69,7 +73,9 @@ void upload(void *&dst, const std::vector<T> &src, hipStream_t s) {
 void batch_upload_views(ofl_batch *b) {
     const size_t n = b->grids.size();
     std::vector<GridView> views(n), swapped(n);
+    b->epochs.resize(n);
     for (size_t g = 0; g < n; ++g) {
+        b->epochs[g] = b->grids[g]->swap_epoch;
         views[g] = b->grids[g]->view;
         views[g].partials = static_cast<double *>(b->d_partials) + b->partial_base[g];
         views[g].nseg = b->nseg.empty() ? 0 : b->nseg[g];
@@ -200,9 +206,85 @@ void xcd_bands(std::vector<SweepItem> &items, size_t first, int per_chunk) {
 
 }  // namespace
 
+namespace {
+
+// The work list of the batch's iterations in pairs: every grid's planes in flat
+// segments, cut into chunks of about the same number of planes, so that items
+// cost about the same; `range` receives each grid's items. Empty where single
+// iterations are better, or asked for by a tile of the caller's.
+//
+// Items run in rounds of one work-group per CU, each chunk + 3 planes long (two
+// margin planes and the fill of the pipeline); the chunk is the one with the
+// fewest plane steps in all. Rows so long that their margins take more than 45%
+// of a work-group's points, and batches whose margins and idle lanes exceed 2.5
+// times their points (slabs and tiny grids, unless the whole batch is small and
+// bound by its launches) stay with single iterations.
+std::vector<PairItem> pair_items(const ofl_batch *b, std::vector<int> *range) {
+    const int n = static_cast<int>(b->grids.size());
+    std::vector<PairItem> items;
+    range->assign(static_cast<size_t>(n) + 1, 0);
+    if (b->tile_chosen || launch_pair_batch == nullptr)
+        return items;
+    std::vector<int> segs(static_cast<size_t>(n));
+    double points = 0.0;
+    int kmax = 0;
+    for (int g = 0; g < n; ++g) {
+        const ofl_grid *q = b->grids[static_cast<size_t>(g)];
+        const int pitch = q->lay.pitch;
+        if (pair_flat_own(pitch, kPairBatchWaves) < 0.55 * 4 * kWave * kPairBatchWaves ||
+            static_cast<long long>(pitch) * q->J > (1LL << 28))
+            return items;
+        segs[static_cast<size_t>(g)] = pair_flat_segments(q->J, pitch);
+        points += static_cast<double>(q->I - 2) * (q->J - 2) * (q->K - 2);
+        kmax = std::max(kmax, q->K - 2);
+    }
+    int best = 0;
+    double best_cost = 0.0, best_work = 0.0;
+    for (int chunk = 1; chunk <= kmax; ++chunk) {
+        double count = 0.0, work = 0.0;
+        for (int g = 0; g < n; ++g) {
+            const int planes = b->grids[static_cast<size_t>(g)]->K - 2;
+            const int parts = (planes + chunk - 1) / chunk;
+            count += static_cast<double>(parts) * segs[static_cast<size_t>(g)];
+            work += (planes + 2.0 * parts) * segs[static_cast<size_t>(g)] * (4 * kWave * kPairBatchWaves);
+        }
+        const double cost = std::ceil(count / b->cu_count) * (chunk + 3);
+        if (best == 0 || cost < best_cost) {
+            best = chunk;
+            best_cost = cost;
+            best_work = work;
+        }
+    }
+    if (best_work > 2.5 * points && points * (b->fmt == OFL_COEF_F32 ? 56 : 32) > 16e6)
+        return items;
+    for (int g = 0; g < n; ++g) {
+        const ofl_grid *q = b->grids[static_cast<size_t>(g)];
+        const int planes = q->K - 2, parts = (planes + best - 1) / best, chunk = (planes + parts - 1) / parts;
+        const int own = pair_flat_own(q->lay.pitch, kPairBatchWaves), first = pair_flat_first(q->lay.pitch);
+        for (int m0 = 1; m0 <= planes; m0 += chunk)
+            for (int s = 0; s < segs[static_cast<size_t>(g)]; ++s)
+                items.push_back({g, first + s * own, m0, std::min(m0 + chunk, q->K - 1)});
+        (*range)[static_cast<size_t>(g) + 1] = static_cast<int>(items.size());
+    }
+    return items;
+}
+
+// How many of a run's iterations go in pairs: all before the last, after an
+// odd one.
+int batch_pairs(const ofl_batch *b, int iters) { return b->p_cnt > 0 && iters >= 3 ? (iters - 1) / 2 : 0; }
+
+}  // namespace
+
 void batch_build_tables(ofl_batch *b) {
-    if (b->tables_ready)
+    if (b->tables_ready) {
+        // another batch that holds one of the grids may have exchanged its buffers
+        for (size_t g = 0; g < b->grids.size(); ++g)
+            if (b->epochs[g] != b->grids[g]->swap_epoch) {
+                batch_upload_views(b);
+                break;
+            }
         return;
+    }
     free_tables(b);
     const int n = static_cast<int>(b->grids.size());
     for (ofl_grid *g : b->grids)
@@ -293,6 +375,14 @@ void batch_build_tables(ofl_batch *b) {
     upload(b->d_sitems, sitems, s);
     upload(b->d_ritems, ritems, s);
     upload(b->d_range, range, s);
+    std::vector<int> prange;
+    const std::vector<PairItem> pitems = pair_items(b, &prange);
+    if (!pitems.empty()) {
+        upload(b->d_pitems, pitems, s);
+        upload(b->d_prange, prange, s);
+        hip_check(hipMalloc(&b->d_pparts, 4 * sizeof(double) * pitems.size()), "hipMalloc(batch pair partials)");
+        b->p_cnt = static_cast<int>(pitems.size());
+    }
     hip_check(hipStreamSynchronize(s), "hipStreamSynchronize(batch tables)");
     b->tables_ready = true;
 }
@@ -320,14 +410,11 @@ int blocks_for(const ofl_batch *b, int nitems) {
 
 }  // namespace
 
-// Enqueue iters x (S, R, finalize, C) for every grid on the batch stream:
-// per nest one batched launch per vector-width class that has work. With
-// OFL_FUSE_RESIDUAL the sweep emits the residual partials (then one finalize
-// per grid); with OFL_FUSE_COPYBACK_SWAP there is no copy-back and odd
-// iterations read the view table with p and wrk2 exchanged.
-void batch_enqueue(ofl_batch *b, int iters, float omega) {
-    const auto *views_even = static_cast<const GridView *>(b->d_views);
-    const auto *views_odd = static_cast<const GridView *>(b->d_views_swapped);
+namespace {
+
+// iters iterations one by one, from the view table *flip, which follows the
+// exchanges.
+void enqueue_single(ofl_batch *b, int iters, float omega, const GridView *const *tables, int *flip) {
     const auto *sitems = static_cast<const SweepItem *>(b->d_sitems);
     const auto *ritems = static_cast<const RowItem *>(b->d_ritems);
     const auto *range = static_cast<const int *>(b->d_range);
@@ -339,7 +426,7 @@ void batch_enqueue(ofl_batch *b, int iters, float omega) {
     // tile.vec 0: every item runs at its grid's own width (views[].vec)
     const int vec = b->tile.vec;
     for (int it = 0; it < iters; ++it) {
-        const GridView *views = (swap && (it & 1)) ? views_odd : views_even;
+        const GridView *views = tables[*flip];
         // fused residual: iteration it writes partial buffer it % 2, and the
         // first work-groups of its sweep sum the previous iteration's buffer
         // into each grid's gosa; the last iteration's is summed after the loop
@@ -365,7 +452,39 @@ void batch_enqueue(ofl_batch *b, int iters, float omega) {
         if (!swap && b->r_cnt > 0)
             launch_batch_copyback(views, ritems, b->r_cnt, vec, b->tile.flags, blocks_for(b, b->r_cnt), b->stream,
                                   true);
+        if (swap)
+            *flip ^= 1;
     }
+}
+
+}  // namespace
+
+// Enqueue iters x (S, R, finalize, C) for every grid on the batch stream:
+// iterations in pairs where the batch has a list for them, the others per nest
+// one batched launch. With OFL_FUSE_RESIDUAL the sweep emits the residual
+// partials (then one finalize per grid); with OFL_FUSE_COPYBACK_SWAP there is no
+// copy-back. Each pair and each such iteration exchanges every grid's p and
+// wrk2, so what follows reads the other view table.
+void batch_enqueue(ofl_batch *b, int iters, float omega) {
+    const GridView *tables[2] = {static_cast<const GridView *>(b->d_views),
+                                 static_cast<const GridView *>(b->d_views_swapped)};
+    int flip = 0;
+    const int pairs = batch_pairs(b, iters);
+    if (pairs == 0) {
+        enqueue_single(b, iters, omega, tables, &flip);
+        return;
+    }
+    if ((iters - 1) & 1)
+        enqueue_single(b, 1, omega, tables, &flip);
+    const auto *items = static_cast<const PairItem *>(b->d_pitems);
+    const auto *range = static_cast<const int *>(b->d_prange);
+    const int n = static_cast<int>(b->grids.size());
+    double *buf[2] = {static_cast<double *>(b->d_pparts), static_cast<double *>(b->d_pparts) + 2LL * b->p_cnt};
+    for (int t = 0; t < pairs; ++t, flip ^= 1)
+        launch_pair_batch(tables[flip], items, b->p_cnt, range, n, b->fmt != OFL_COEF_F32, omega, buf[t & 1],
+                          t > 0 ? buf[(t - 1) & 1] : nullptr, b->stream);
+    launch_pair_batch_fold(tables[flip], buf[(pairs - 1) & 1], b->p_cnt, range, n, omega, b->stream);
+    enqueue_single(b, 1, omega, tables, &flip);
 }
 
 void batch_prepare(ofl_batch *b) {
@@ -423,10 +542,12 @@ void batch_mark_done(ofl_batch *b, int iters) {
     }
 }
 
-// After a swapping run of odd length every grid's p lives in its former
-// wrk2 buffer: record the exchange and refresh both view tables in place.
+// After an odd number of exchanges every grid's p lives in its former wrk2
+// buffer: record that and refresh both view tables in place.
 void batch_after_run(ofl_batch *b, int iters) {
-    if ((b->fusion & OFL_FUSE_COPYBACK_SWAP) && (iters & 1)) {
+    const int pairs = batch_pairs(b, iters);
+    const int exchanges = pairs + ((b->fusion & OFL_FUSE_COPYBACK_SWAP) ? iters - 2 * pairs : 0);
+    if (exchanges & 1) {
         for (ofl_grid *g : b->grids)
             grid_swap_p_wrk2(g);
         batch_upload_views(b);

@@ -31,6 +31,15 @@ struct ofl_batch {
     int s_cnt = 0;  // sweep items (every grid's, largest grid first)
     int r_cnt = 0;  // residual/copy-back items
 
+    // Iterations in pairs (pair.hip): a work list of its own, empty where the
+    // batch runs every iteration by itself.
+    void *d_pitems = nullptr;
+    void *d_prange = nullptr;  // per grid, its range of the list
+    void *d_pparts = nullptr;  // two buffers of two partial sums per item
+    int p_cnt = 0;
+
+    std::vector<unsigned> epochs;   // per grid, its exchanges of p and wrk2 when the views were uploaded
+
     std::vector<int> gvec;          // per grid, its points per lane in the batch
 
     std::vector<int> partial_base;  // per grid, its first residual partial

@@ -290,6 +290,9 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
     typedef typename VecOf<VEC>::F F;
     typedef Coefs<VEC, BF16> C12;
     constexpr bool kDma = Shared<VEC, BF16, W>::kDma;
+    // bfloat16 is decoded once for both steps where registers allow: the flat
+    // form's lane masks leave too few.
+    constexpr bool kDecoded = kDma && !(BF16 && FLAT);
     constexpr int S = kWave * VEC;
     constexpr int kEb = BF16 ? 2 : 4;
     const int lane = threadIdx.x & (kWave - 1);
@@ -299,6 +302,11 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
     // The lane's points: i0.. of row j; its loads at `pos` elements from the
     // (wave-uniform) line starts la, lc, lb of rows j-1, j, j+1 in p. Positions
     // outside the arrays are clamped; what is loaded there is never stored.
+    // Flat form: a point's place in the coefficient planes, whose rows may have a
+    // pitch of their own, for a load of n points.
+    auto coef_at = [&](int f, int n) {
+        return g.cpitch == pitch ? f : f / pitch * g.cpitch + min(f % pitch, g.cpitch - n);
+    };
     int i0, j, pos, cpos;
     long long la, lc, lb, cline;
     bool row_in, row_out, own, shared_rows;
@@ -308,13 +316,13 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
         pos = min(max(f, 0), last);
         j = pos / pitch;
         i0 = pos - j * pitch;
-        cpos = pos;
+        cpos = coef_at(pos, VEC);
         lc = cline = 0;
         la = -static_cast<long long>(pitch);
         lb = pitch;
         row_in = f == pos && j >= 1 && j <= g.J - 2;
         own = f == pos && f >= own_lo && f < own_hi;
-        row_out = row_in && own;
+        row_out = row_in;
         shared_rows = ts + wave * S < own_lo + pitch || ts + (wave + 1) * S > own_hi - pitch;
     } else {
         j = j0 - 1 + wave;
@@ -411,10 +419,12 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
 
     // Coefficients to LDS: FP32, one load per coefficient; bfloat16, one load
     // for two (half a wave's 16-byte loads cover its 256 points).
-    const unsigned db = BF16 ? static_cast<unsigned>(FLAT ? min(max(ts + wave * S + (lane & 31) * 8, 0), pitch * g.J - 8)
-                                                          : min(ts + (lane & 31) * 8, g.cpitch - 8)) *
-                                   2
-                             : cb;
+    unsigned db = cb;
+    if constexpr (BF16) {
+        const int at8 = (lane & 31) * 8;
+        db = 2u * static_cast<unsigned>(
+                      FLAT ? coef_at(min(max(ts + wave * S + at8, 0), pitch * g.J - 8), 8) : min(ts + at8, g.cpitch - 8));
+    }
     auto dma = [&](int t, int k, auto nt) {
         constexpr int kAux = decltype(nt)::value ? 2 : 0;
         auto *dst = (OFL_LDS void *)&sh.next[wd][kDma ? t : 0][0];
@@ -468,8 +478,7 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
         nr = load_rows(m0);
     }
 
-    Coefs<VEC, false> lagd;  // plane m-1's coefficients: decoded where registers allow,
-    C12 lag;                 // as stored otherwise
+    Coefs<VEC, BF16 && !kDecoded> lag;  // plane m-1's coefficients
     double r1 = 0.0, r2 = 0.0;
     float o[VEC];
     auto store = [&](int k) {
@@ -529,15 +538,14 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
         }
         __builtin_amdgcn_sched_barrier(0);
         plane_of(r, n);
-        Coefs<VEC, false> D;
-        if constexpr (kDma)
+        Coefs<VEC, BF16 && !kDecoded> D;
+        if constexpr (BF16 && kDecoded)
             decode<VEC, BF16>(g, C, D);
+        else
+            D = C;
         float u[VEC];
         if (active && m >= 1 && m <= g.K - 2) {
-            if constexpr (kDma)
-                relax<VEC, false>(g, w1, n, D, omega, u);
-            else
-                relax<VEC, BF16>(g, w1, n, C, omega, u);
+            relax(g, w1, n, D, omega, u);
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 u[e] = in[e] ? u[e] : w1.m.c[e];
@@ -576,10 +584,7 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
                 n2.c[e] = u[e];
             n2.derive(hm);
             if (m > m0) {
-                if constexpr (kDma)
-                    relax<VEC, false>(g, w2, n2, lagd, omega, o);
-                else
-                    relax<VEC, BF16>(g, w2, n2, lag, omega, o);
+                relax(g, w2, n2, lag, omega, o);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
                     o[e] = in[e] ? o[e] : w2.m.c[e];
@@ -593,10 +598,7 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
             }
             w2.slide(n2);
         }
-        if constexpr (kDma)
-            lagd = D;
-        else
-            lag = C;
+        lag = D;
         // step 2's plane m+1 lies beside the boundary column of p's plane m+1
         if constexpr (!FLAT)
             hm = spread(r.h);
@@ -662,6 +664,48 @@ __global__ __launch_bounds__(W *kWave) void pair_fold_kernel(const double *parts
     }
 }
 
+// Many grids in flat form, one item per work-group. parts: two sums per item;
+// range[b], range[b+1]: the items of grid b. The last ngrids work-groups turn
+// the previous pair's sums (prev, may be null) into each grid's gosa.
+template <bool BF16, int W>
+__global__ __launch_bounds__(W *kWave) void pair_batch_kernel(const GridView *__restrict__ views,
+                                                              const PairItem *__restrict__ items, int nitems,
+                                                              const int *__restrict__ range, float omega,
+                                                              double *parts, const double *prev) {
+    __shared__ Shared<4, BF16, W> sh;
+    if (static_cast<int>(blockIdx.x) >= nitems) {
+        const int b = blockIdx.x - nitems;
+        if (prev)
+            for (int q = 0; q < 2; ++q) {
+                const double t = group_sum<W>(prev + static_cast<long long>(q) * nitems + range[b],
+                                              range[b + 1] - range[b], sh.wsum[0]);
+                if (threadIdx.x == 0)
+                    *views[b].gosa = t / (static_cast<double>(omega) * static_cast<double>(omega));
+            }
+        return;
+    }
+    const int w = xcd_range(blockIdx.x, nitems);
+    const PairItem item = items[w];
+    const GridView g = views[item.grid];
+    const int h = pair_flat_margin(g.pitch);
+    pair_march<4, BF16, W, true>(g, sh, item.first - h, 0, item.first, item.first + pair_flat_own(g.pitch, W), item.m0,
+                                 item.m1, omega, parts + w, nitems);
+}
+
+template <int W>
+__global__ __launch_bounds__(W *kWave) void pair_batch_fold_kernel(const GridView *__restrict__ views,
+                                                                   const double *__restrict__ parts, int nitems,
+                                                                   const int *__restrict__ range, double omega) {
+    __shared__ double wsum[W];
+    const int b = blockIdx.x;
+    for (int q = 0; q < 2; ++q) {
+        const double t = group_sum<W>(parts + static_cast<long long>(q) * nitems + range[b], range[b + 1] - range[b],
+                                      wsum);
+        if (threadIdx.x == 0)
+            *views[b].gosa = t / (omega * omega);
+    }
+}
+
 template <int VEC, bool BF16, int W>
 void go(const GridView &g, const PairShape &s, float omega, double *parts, const double *prev, hipStream_t st) {
     pair_kernel<VEC, BF16, W><<<s.blocks() + 1, W * kWave, 0, st>>>(g, s, omega, parts, prev);
@@ -691,6 +735,24 @@ void launch_pair(const GridView &g, int bf16, const PairShape &s, float omega, d
     else
         fail(OFL_EINVAL, "pair sweep: no such shape");
     hip_check(hipGetLastError(), "pair sweep launch");
+}
+
+void launch_pair_batch(const GridView *views, const PairItem *items, int nitems, const int *range, int ngrids, int bf16,
+                       float omega, double *parts, const double *prev, hipStream_t st) {
+    const int blocks = nitems + ngrids;
+    if (bf16)
+        pair_batch_kernel<true, kPairBatchWaves>
+            <<<blocks, kPairBatchWaves * kWave, 0, st>>>(views, items, nitems, range, omega, parts, prev);
+    else
+        pair_batch_kernel<false, kPairBatchWaves>
+            <<<blocks, kPairBatchWaves * kWave, 0, st>>>(views, items, nitems, range, omega, parts, prev);
+    hip_check(hipGetLastError(), "batched pair sweep launch");
+}
+
+void launch_pair_batch_fold(const GridView *views, const double *parts, int nitems, const int *range, int ngrids,
+                            float omega, hipStream_t st) {
+    pair_batch_fold_kernel<8><<<ngrids, 8 * kWave, 0, st>>>(views, parts, nitems, range, static_cast<double>(omega));
+    hip_check(hipGetLastError(), "batched pair sweep residual launch");
 }
 
 void launch_pair_fold(const double *parts, const PairShape &s, float omega, double *gosa, hipStream_t st) {

@@ -94,6 +94,26 @@ inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *
     return best->vec != 0;
 }
 
+// Flat form, for a batch's grids: a work-group covers 256 * kPairBatchWaves
+// consecutive points of a plane, whatever the row length, and owns those that
+// lie a row and a point from either end (in whole 16-byte loads of bfloat16).
+constexpr int kPairBatchWaves = 8;
+__host__ __device__ inline constexpr int pair_flat_margin(int pitch) { return (pitch + 1 + 7) / 8 * 8; }
+__host__ __device__ inline constexpr int pair_flat_own(int pitch, int waves) {
+    return waves * kWave * 4 - 2 * pair_flat_margin(pitch);
+}
+// The first owned point of a plane's first work-group, and how many there are.
+inline int pair_flat_first(int pitch) { return pitch / 8 * 8; }
+inline int pair_flat_segments(int J, int pitch) {
+    const int own = pair_flat_own(pitch, kPairBatchWaves);
+    return ((J - 1) * pitch - pair_flat_first(pitch) + own - 1) / own;
+}
+
+// A work-group's share of a batch: grid, first owned point, planes [m0, m1).
+struct PairItem {
+    int grid, first, m0, m1;
+};
+
 // parts: 2 * blocks() doubles, every one written; prev: the previous pair's
 // parts (same shape), whose two residuals this launch turns into gosa, or null.
 // Weak: the host code also links without the device code (it then runs every
@@ -103,5 +123,13 @@ __attribute__((weak)) void launch_pair(const GridView &g, int bf16, const PairSh
 // The last pair's two residuals into gosa.
 __attribute__((weak)) void launch_pair_fold(const double *parts, const PairShape &s, float omega, double *gosa,
                                             hipStream_t st);
+
+// The same for a batch: views of every grid, items grid by grid (grid b owns
+// items range[b] .. range[b+1]-1), 2 * nitems partial sums.
+__attribute__((weak)) void launch_pair_batch(const GridView *views, const PairItem *items, int nitems,
+                                             const int *range, int ngrids, int bf16, float omega, double *parts,
+                                             const double *prev, hipStream_t st);
+__attribute__((weak)) void launch_pair_batch_fold(const GridView *views, const double *parts, int nitems,
+                                                  const int *range, int ngrids, float omega, hipStream_t st);
 
 }  // namespace ofl

@@ -97,3 +97,69 @@ def test_pairs_replay_and_continue():
     assert ofl.ofl_residual(one.handle) == ofl.ofl_residual(two.handle)
     one.close()
     two.close()
+
+
+# ------------------------------------------------------------------ batches
+
+
+def run_batch(probs, aligns, fmt, iters_list, own_tile, fusion=0):
+    """own_tile: the default tile set by the caller, which keeps single iterations."""
+    grids = [ofl.Grid(a, coef_format=fmt, row_align=ra) for a, ra in zip(probs, aligns)]
+    b = ofl.ofl_batch_create([g.handle for g in grids])
+    ofl.ofl_batch_set_fusion(b, fusion)
+    if own_tile:
+        ofl.ofl_batch_set_tile(b, ofl.ofl_batch_get_tile(b))
+    gosa = [ofl.ofl_batch_run(b, n, OMEGA, len(grids)) for n in iters_list]
+    ofl.ofl_batch_destroy(b)
+    out = [g.p.copy() for g in grids]
+    for g in grids:
+        g.close()
+    return out, gosa
+
+
+# Planes shorter than a work-group's 2048 points, of several work-groups, ending
+# on and off their bounds; pitches on and off multiples of 8; one row; few planes.
+BATCHES = [
+    [(3, 3, 3), (5, 4, 6)],
+    [(33, 33, 65), (34, 66, 9), (36, 60, 12), (62, 130, 5)],
+    [(161, 40, 20), (97, 41, 31), (129, 33, 9)],
+    [(300, 7, 6), (33, 3, 40), (41, 23, 37)],
+]
+
+
+@pytest.mark.parametrize("fusion", [0, FUSE_ALL])
+@pytest.mark.parametrize("fmt", [ofl.OFL_COEF_F32, ofl.OFL_COEF_BF16_OFFSET])
+@pytest.mark.parametrize("shapes", BATCHES, ids=str)
+def test_batch_pairs_equal_single_iterations(shapes, fmt, fusion):
+    say("batch pairs", shapes, "format", fmt, "fusion", fusion)
+    probs = [synth.make_problem(*s, seed=synth.grid_seed(70 + t)) for t, s in enumerate(shapes)]
+    for aligns in ([4] * len(probs), [0, 8, 4, 32][:len(probs)]):
+        iters = [3, 6, 6, 5]
+        p1, g1 = run_batch(probs, aligns, fmt, iters, True, fusion)
+        p2, g2 = run_batch(probs, aligns, fmt, iters, False, fusion)
+        for x, y in zip(p1, p2):
+            assert np.array_equal(x, y)
+        assert g1 == g2
+
+
+def test_two_batches_share_a_grid():
+    """Pairs exchange a grid's buffers: another batch that holds it follows."""
+    say("batches sharing a grid")
+    probs = [synth.make_problem(41, 23, 37, seed=8), synth.make_problem(33, 20, 12, seed=9)]
+    ref = [ofl.Grid(a, row_align=4) for a in probs]
+    grids = [ofl.Grid(a, row_align=4) for a in probs]
+    one = ofl.ofl_batch_create([grids[0].handle, grids[1].handle])
+    two = ofl.ofl_batch_create([grids[0].handle])
+    done = 0
+    for b, n in ((one, 4), (two, 4), (one, 7), (two, 3), (one, 3)):
+        ofl.ofl_batch_run(b, n, OMEGA, 2 if b is one else 1)
+        done += n
+    for g, n in zip(ref, (done, 14)):
+        ofl.ofl_set_profiling(g.handle, True)
+        ofl.ofl_jacobi_run(g.handle, n, OMEGA)
+    for g, r in zip(grids, ref):
+        assert np.array_equal(g.p, r.p)
+    ofl.ofl_batch_destroy(two)
+    ofl.ofl_batch_destroy(one)
+    for g in grids + ref:
+        g.close()
