@@ -539,7 +539,11 @@ int ofl_grid_search_loops(ofl_grid *g, const ofl_ga_params *ga, int iters, float
 /* Matrix product C = A B of row-major FP32 matrices in device memory: A is
  * M x K with row stride lda >= K, B is K x N with ldb >= N, C is M x N with
  * ldc >= N (strides in elements). C must not overlap A or B. The library's
- * matrix-core kernel (FP32 products, FP32 accumulation) is queued on stream (a
+ * matrix-core kernels are queued (small and narrow products: FP32 instructions;
+ * large ones: each value as the exact sum of three bfloat16 parts, six part
+ * products, FP32 accumulation, with tiles whose values leave that form's range
+ * computed in FP32; either way closer to the exact product than one FP32 sum
+ * over K, infinities and NaN as defined) on stream (a
  * hipStream_t; NULL: the default stream) and the call returns without
  * waiting. Nothing is read or written when M or N is 0; K = 0 sets C to 0.
  * EINVAL for negative sizes, M above 65535 * 128, short strides, or a NULL

@@ -2,25 +2,26 @@
 // matrix-product block is replaced with (function-block offload, Sec. 3.2.2,
 // Sec. 4.2.1).
 //
-// C = A B for row-major FP32 matrices. A work-group of four waves owns a
-// 128 x 256 tile of C. Each wave owns a 64 x 128 quarter as 2 x 4 accumulator
-// tiles of 32 x 32, updated by v_mfma_f32_32x32x2_f32 (FP32 operands, FP32
-// accumulation); each operand value read from LDS feeds two or four products.
-// Products whose 128-row tiles leave much of their last round of resident
-// work-groups idle use 64 x 256 tiles (four waves of 64 x 64 side by side),
-// twice as many (see launch_gemm_f32). The K dimension advances in stages of
-// 16: the next stage's A and B tiles are fetched from global memory into
-// registers while the current stage, held in LDS, feeds the matrix cores. LDS
-// is double-buffered, so one barrier per stage suffices.
+// C = A B for row-major FP32 matrices, in two forms; launch_gemm_f32 picks.
 //
-// Tiles are handed to work-groups so that each XCD works through a contiguous
-// run of them. Measured at 4096^3 with 128 x 128 tiles, this order ran at up
-// to 132 TFLOP/s against 118 for the hardware's round-robin, but from run to
-// run it varied down to the round-robin figure; 128 x 256 tiles ran at 137.
+// Split form (large products): 128 x 128 tiles staged through LDS, each FP32
+// value as the exact sum of three bfloat16 parts, multiplied on the bfloat16
+// matrix instructions with FP32 accumulation. Direct form (small and narrow
+// products): tiles of 16 x 16 to 32 x 32 on the FP32 matrix instructions, K
+// shared among a work-group's waves, operands straight from global memory.
 //
-// Operand layout of the 32x32x2 instruction (wave64): lane l supplies
-// A[l % 32][l / 32] and B[l / 32][l % 32]; accumulator register r of lane l
-// holds C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
+// Both add up K in several partial sums, which brings the error against FP64
+// below that of one FP32 sum over all of K: measured as a fraction of that
+// sum's, root mean square over C, 0.26-0.74 for the direct form and 0.60-0.89
+// for the split form (K from 64 to 8192, normally distributed values; at K = 32
+// the direct form's sum has one part and the fraction is 1).
+//
+// Operand layouts (wave64, lane l): the 32x32x2 FP32 instruction takes
+// A[l % 32][l / 32] and B[l / 32][l % 32], the 16x16x4 one A[l % 16][l / 16] and
+// B[l / 16][l % 16], the 32x32x16 bfloat16 one eight consecutive k from
+// 8 (l / 32) of row (column) l % 32. Accumulator register r holds row
+// 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32 of a 32 x 32 tile, and row
+// 4 (l / 16) + r, column l % 16 of a 16 x 16 one.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -31,29 +32,15 @@ namespace ofl {
 
 namespace {
 
-constexpr int kGemmThreads = 256;
-constexpr int kTileN = 256, kTileK = 16;
-constexpr int kCus = 256;  // compute units of an MI355X
-
-// Work-group tile of TM x 256: four waves of 64 rows each, TM / 64 of them along
-// m and the rest along n; each thread fetches kAPer consecutive k of one A row.
-template <int TM>
-struct Shape {
-    static constexpr int kWavesM = TM / 64;
-    static constexpr int kWavesN = 4 / kWavesM;
-    static constexpr int kNJ = kTileN / kWavesN / 32;  // 32-wide accumulator tiles per wave along n
-    static constexpr int kAPer = TM * kTileK / kGemmThreads;
-    static constexpr int kAThreadsPerRow = kTileK / kAPer;
-    static_assert(kWavesM * kWavesN == kGemmThreads / 64 && kAPer % 4 == 0, "unsupported tile");
-};
-constexpr int kBThreadsPerRow = kTileN / 8;                 // threads loading one B row, 8 floats each
-constexpr int kBRowsPerPass = kGemmThreads / kBThreadsPerRow;
-constexpr int kBPasses = kTileK / kBRowsPerPass;            // passes over the B tile per stage
-static_assert(kBPasses * kBRowsPerPass == kTileK, "B tile rows must split into whole passes");
-constexpr int kLdsPad = 4;  // floats of padding per LDS row
 constexpr int kXcds = 8;    // accelerator complex dies of an MI355X, each with its own L2
+constexpr int kCus = 256;   // compute units of an MI355X
 
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+// four consecutive floats that start on any element (a global load needs
+// 4-byte alignment only)
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 struct GemmArgs {
     int M, N, K;
@@ -65,185 +52,480 @@ struct GemmArgs {
     int ldc;
 };
 
-// Fetch this thread's share of the A (TM x 16) and B (16 x 256) tiles at k0
-// into registers: A row tid / kAThreadsPerRow, kAPer columns from
-// (tid % kAThreadsPerRow) * kAPer; B rows pass * 8 + tid / 32, columns
-// (tid % 32) * 8 .. +8, for pass 0 and 1. Out-of-range elements read as zero.
-// `vec`: the block's tiles lie inside the matrices and every row start is
-// 16-byte aligned, so whole float4 loads are used.
-template <int TM>
-__device__ __forceinline__ void fetch(const GemmArgs &g, int m0, int n0, int k0, bool vec, float *ra, float *rb) {
-    using S = Shape<TM>;
-    const int tid = threadIdx.x;
-    const int am = m0 + tid / S::kAThreadsPerRow, ak = k0 + (tid % S::kAThreadsPerRow) * S::kAPer;
-    const int bn = n0 + (tid % kBThreadsPerRow) * 8;
-    if (vec && k0 + kTileK <= g.K) {
-        const float4 *pa = reinterpret_cast<const float4 *>(g.A + static_cast<size_t>(am) * g.lda + ak);
-#pragma unroll
-        for (int q = 0; q < S::kAPer / 4; ++q) {
-            const float4 a = pa[q];
-            ra[4 * q] = a.x; ra[4 * q + 1] = a.y; ra[4 * q + 2] = a.z; ra[4 * q + 3] = a.w;
-        }
-#pragma unroll
-        for (int pass = 0; pass < kBPasses; ++pass) {
-            const int bk = k0 + pass * kBRowsPerPass + tid / kBThreadsPerRow;
-            const float4 *pb = reinterpret_cast<const float4 *>(g.B + static_cast<size_t>(bk) * g.ldb + bn);
-            const float4 b0 = pb[0], b1 = pb[1];
-            float *r = rb + pass * 8;
-            r[0] = b0.x; r[1] = b0.y; r[2] = b0.z; r[3] = b0.w;
-            r[4] = b1.x; r[5] = b1.y; r[6] = b1.z; r[7] = b1.w;
-        }
-        return;
+// Work-groups are dealt round-robin to the eight XCDs. Give each XCD a
+// contiguous run of tiles in row-major tile order instead, so that tiles
+// sharing rows of A (and neighbouring columns of B) meet in one XCD's L2.
+__device__ __forceinline__ int tile_index() {
+    const int n = gridDim.x, b = blockIdx.x, per = n / kXcds;
+    return b < per * kXcds ? (b % kXcds) * per + b / kXcds : b;
+}
+
+// ---- direct form
+//
+// All KS waves of a work-group compute the same tile of C, each over its own
+// chunks of 32 k, dealt in turn (whole 128-byte lines of A's rows), and their
+// sums are added in wave order through LDS. A lane loads four consecutive k of
+// its A row in one 16-byte load, and the four instructions that use them take k
+// in that order (any order of k serves as long as A and B agree), so operands
+// need no staging and there is no barrier before the sum: one wave's loads hide
+// behind the others' instructions.
+//
+// Bound by the loads of a tile's operands through L2, or by the latency of one
+// wave's share where there are few tiles. Measured, us against the former 64- or
+// 128-row by 256-column tiles: 8192 x 16 x 4096 22.1 against 566 (135 MB, 6.1
+// TB/s), 511 x 333 x 1001 with odd strides 9.6 against 183, 1000^3 30.6 against
+// 188, 128 x 128 x 4096 12.2 against 611, 64 x 4096 x 512 6.3 against 129.
+template <int BASE>
+struct Mfma;
+template <>
+struct Mfma<32> {
+    typedef floatx16 Acc;
+    static constexpr int kRegs = 16, kGroups = 2;  // accumulator registers, k values per instruction
+    static __device__ __forceinline__ Acc mul(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
     }
-#pragma unroll
-    for (int e = 0; e < S::kAPer; ++e) {
-        const int k = ak + e;
-        ra[e] = (am < g.M && k < g.K) ? g.A[static_cast<size_t>(am) * g.lda + k] : 0.f;
+    static __device__ __forceinline__ int row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+};
+template <>
+struct Mfma<16> {
+    typedef floatx4 Acc;
+    static constexpr int kRegs = 4, kGroups = 4;
+    static __device__ __forceinline__ Acc mul(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
+
+constexpr int kChunk = 32;
+
+// One wave's sum over chunks first, first + step, ... of K (the last, partial
+// chunk among them) of the MT x 1 accumulator tiles at rows m0.., columns n0,
+// n0 + COLS, ... Rows and columns beyond the matrix are clamped; their sums are
+// never stored.
+template <int BASE, int MT, int COLS = 1>
+__device__ __forceinline__ void direct_sum(const GemmArgs &g, int m0, int n0, int lane, int first, int step,
+                                           typename Mfma<BASE>::Acc (&acc)[MT]) {
+    typedef Mfma<BASE> Op;
+    constexpr int kStep = 4 * Op::kGroups;  // k per A load
+    constexpr int kSteps = kChunk / kStep;
+    const int col = lane % BASE, grp = lane / BASE;
+    const float *pa[MT];
 #pragma unroll
-    for (int pass = 0; pass < kBPasses; ++pass) {
-        const int bk = k0 + pass * kBRowsPerPass + tid / kBThreadsPerRow;
+    for (int i = 0; i < MT; ++i) {
+        pa[i] = g.A + static_cast<size_t>(min(m0 + i * BASE + col, g.M - 1)) * g.lda + 4 * grp;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int n = bn + e;
-            rb[pass * 8 + e] = (bk < g.K && n < g.N) ? g.B[static_cast<size_t>(bk) * g.ldb + n] : 0.f;
+        for (int r = 0; r < Op::kRegs; ++r)
+            acc[i][r] = 0.f;
+    }
+    const float *pb = g.B + min(n0 + COLS * col, g.N - 1);
+    struct Chunk {
+        float a[MT][kSteps][4];
+        float b[kSteps][4];
+    };
+    auto load = [&](int k0, Chunk &c) {
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const float4u v = *reinterpret_cast<const float4u *>(pa[i] + k0 + s * kStep);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    c.a[i][s][q] = v[q];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                c.b[s][q] = pb[static_cast<size_t>(k0 + s * kStep + 4 * grp + q) * g.ldb];
+        }
+    };
+    auto mul = [&](const Chunk &c) {
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    acc[i] = Op::mul(c.a[i][s][q], c.b[s][q], acc[i]);
+    };
+    // whole chunks, the next one's loads ahead of this one's products
+    const int chunks = g.K / kChunk;
+    if (first < chunks) {
+        Chunk c0;
+        load(first * kChunk, c0);
+        for (int c = first; c < chunks; c += step) {
+            Chunk c1;
+            if (c + step < chunks)
+                load((c + step) * kChunk, c1);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(c0);
+            c0 = c1;
+        }
+    }
+    // the last K % 32, element by element, by the wave whose turn it is
+    if (g.K % kChunk != 0 && first == chunks % step) {
+        Chunk c;
+        const int k0 = chunks * kChunk;
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int k = k0 + s * kStep + 4 * grp + q;
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    c.a[i][s][q] = k < g.K ? pa[i][k0 + s * kStep + q] : 0.f;
+                c.b[s][q] = k < g.K ? pb[static_cast<size_t>(k) * g.ldb] : 0.f;
+            }
+        mul(c);
+    }
+}
+
+template <int BASE, int MT, int KS>
+__global__ __launch_bounds__(KS * 64) void gemm_direct_kernel(GemmArgs g, int tiles_n) {
+    typedef Mfma<BASE> Op;
+    constexpr int TM = BASE * MT;
+    __shared__ float sums[KS][TM][BASE];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t = tile_index();
+    const int m0 = t / tiles_n * TM, n0 = t % tiles_n * BASE;
+    typename Op::Acc acc[MT];
+    direct_sum<BASE, MT>(g, m0, n0, lane, wave, KS, acc);
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int r = 0; r < Op::kRegs; ++r)
+            sums[wave][i * BASE + Op::row(lane, r)][lane % BASE] = acc[i][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < TM * BASE; e += KS * 64) {
+        const int r = e / BASE, c = e % BASE;
+        float v = sums[0][r][c];
+#pragma unroll
+        for (int w = 1; w < KS; ++w)
+            v += sums[w][r][c];
+        if (m0 + r < g.M && n0 + c < g.N)
+            g.C[static_cast<size_t>(m0 + r) * g.ldc + n0 + c] = v;
+    }
+}
+
+// ---- split form
+//
+// x = x0 + x1 + x2 with x0 = bfloat16(x), x1 = bfloat16(x - x0),
+// x2 = x - x0 - x1, each rounded to nearest even: FP32's 24 significant bits fit
+// three bfloat16 ones of 8, so the sum is exact. Of the nine products of parts,
+// the six whose part indices add up to at most 2 are taken; what is left out is
+// below 2^-25 of |a b|, an FP32 product's own rounding. Six bfloat16
+// instructions do the work of eight FP32 ones in 3/8 of the matrix cores' time.
+//
+// Four waves own a 128 x 128 tile (64 x 64 each). A stage of 32 k is fetched
+// into registers, split there and written to LDS in the order the instructions
+// read it; each value is split once and feeds 128 rows or columns. A work-group
+// has two such groups of four waves on one tile: they take alternate stages, one
+// splits while the other multiplies, and their sums are added at the end. With
+// one group, two work-groups share a CU instead (at small K, see pick_form).
+//
+// Measured, us against the former FP32-instruction tiles: 4096^3 724 against 988
+// (190 TFLOP/s), 8192^3 5925 against 7834, 2048^3 95 against 173, 2340 x 1142 x
+// 3098 124 against 594. The bfloat16 instructions then run at 1.14 PFLOP/s, the
+// rate a library's large bfloat16 product reaches on this card (1.11), whose
+// clock falls below 2 GHz under it.
+//
+// Values outside the split's range: parts of |x| < 2^-50 could fall below the
+// smallest normal number, and x beyond bfloat16's largest, infinite or NaN gives
+// infinite or NaN parts. A tile that met the former, or whose sums came out
+// infinite or NaN, is computed again with the FP32 instructions.
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
+constexpr int kSplitTile = 128, kSplitK = 32, kParts = 3;
+// One part of 32 rows x 32 k in LDS: 8 k of a row are 16 bytes, 32 rows 512, and
+// 32 bytes more put the k groups that 16 consecutive lanes write of A (8 bytes
+// each, two rows) on distinct banks. B's columns are dealt to the four 32-column
+// tiles in turn (tile e: columns 4 c + e), so that a lane's four consecutive
+// columns go to the same row of the four tiles, and 16 consecutive lanes write
+// both halves of eight rows. No access conflicts (with k groups 640 bytes apart
+// and columns in order, a stage's 48 accesses per wave took 330 cycles more).
+constexpr int kK8Stride = 512 + 32, kTileStride = 4 * kK8Stride;
+constexpr unsigned kTinyBits = (127u - 50u) << 24;  // 2^-50, shifted left by one (no sign)
+
+__device__ __forceinline__ void split2(float x, float y, unsigned (&p)[kParts]) {
+#pragma unroll
+    for (int s = 0; s < kParts; ++s) {
+        const bf2 h = __builtin_convertvector(floatx2{x, y}, bf2);
+        p[s] = __builtin_bit_cast(unsigned, h);
+        if (s + 1 < kParts) {
+            x -= __uint_as_float(p[s] << 16);
+            y -= __uint_as_float(p[s] & 0xffff0000u);
         }
     }
 }
 
-template <int TM>
-__global__ __launch_bounds__(kGemmThreads) void gemm_f32_kernel(GemmArgs g, int vec_ok) {
-    using S = Shape<TM>;
-    constexpr int kNJ = S::kNJ;
-    // A is kept transposed (k-major) so that a wave's operand fetch for one k
-    // reads 32 consecutive floats.
-    __shared__ float As[2][kTileK][TM + kLdsPad];
-    __shared__ float Bs[2][kTileK][kTileN + kLdsPad];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int wm = (wave / S::kWavesN) * 64, wn = (wave % S::kWavesN) * (kTileN / S::kWavesN);
-    // Work-groups are dealt round-robin to the eight XCDs. Give each XCD a
-    // contiguous run of tiles in row-major tile order instead, so that tiles
-    // sharing rows of A (and neighbouring columns of B) meet in one XCD's L2.
-    int bx = blockIdx.x, by = blockIdx.y;
-    {
-        const int nb = gridDim.x * gridDim.y, b = blockIdx.y * gridDim.x + blockIdx.x;
-        const int per = nb / kXcds;
-        const int t = b < per * kXcds ? (b % kXcds) * per + b / kXcds : b;
-        by = t / gridDim.x;
-        bx = t % gridDim.x;
-    }
-    const int m0 = by * TM, n0 = bx * kTileN;
-    const bool vec = vec_ok && m0 + TM <= g.M && n0 + kTileN <= g.N;
+// Orders the work-group's LDS accesses without waiting for its global loads
+// (the next stage's are in flight).
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
-    floatx16 acc[2][kNJ];
+template <int GROUPS>
+__global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g, int tiles_n) {
+    __shared__ __attribute__((aligned(16))) char lds[GROUPS][2][kParts * 4 * kTileStride];
+    __shared__ int redo;
+    const int tid = threadIdx.x % 256, lane = tid & 63;
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char *la = lds[group][0], *lb = lds[group][1];
+    const int t = tile_index();
+    const int m0 = t / tiles_n * kSplitTile, n0 = t % tiles_n * kSplitTile;
+    const bool whole_n = n0 + kSplitTile <= g.N;
+
+    // this thread's share of a stage: A rows ar + 32 i, k ak .. ak+3; B rows
+    // bk .. bk+3, columns bn .. bn+3
+    const int ar = tid / 8, ak = tid % 8 * 4;
+    const int bk = (tid / 64 * 2 + tid % 2) * 4, bn = tid % 64 / 2 * 4;
+    const float *pa[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        pa[i] = g.A + static_cast<size_t>(min(m0 + ar + 32 * i, g.M - 1)) * g.lda + ak;
+    // past B's last column a thread's load moves back to start at bs; its values
+    // move up when they are split (there, so that the loads stay in flight)
+    const int bs = min(n0 + bn, max(g.N - 4, 0)), over = n0 + bn - bs;
+    float ra[4][4], rb[4][4];
+    auto fetch = [&](int k0) {
+        if (k0 + kSplitK <= g.K) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4u v = *reinterpret_cast<const float4u *>(pa[i] + k0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    ra[i][q] = v[q];
+            }
+            if (g.N >= 4) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4u v =
+                        *reinterpret_cast<const float4u *>(g.B + static_cast<size_t>(k0 + bk + q) * g.ldb + bs);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        rb[q][e] = v[e];
+                }
+                return;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    ra[i][q] = k0 + ak + q < g.K ? pa[i][k0 + q] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                rb[q][e] = k0 + bk + q < g.K
+                               ? g.B[static_cast<size_t>(k0 + bk + q) * g.ldb + min(bs + e, g.N - 1)]
+                               : 0.f;
+    };
+    unsigned tiny = 0xffffffffu;  // smallest nonzero |x| seen, shifted left, less one (zero wraps to the top)
+    auto stash = [&] {
+        auto put = [&](char *base, int tile, int row, int k, const float *v) {
+            unsigned lo[kParts], hi[kParts];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                tiny = min(tiny, (__float_as_uint(v[q]) << 1) - 1u);
+            split2(v[0], v[1], lo);
+            split2(v[2], v[3], hi);
+#pragma unroll
+            for (int s = 0; s < kParts; ++s)
+                *reinterpret_cast<uintx2 *>(base + (s * 4 + tile) * kTileStride + k / 8 * kK8Stride + row * 16 +
+                                            k % 8 * 2) = uintx2{lo[s], hi[s]};
+        };
+        if (!whole_n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float *v = rb[q];
+                if (over & 1)
+                    v[0] = v[1], v[1] = v[2], v[2] = v[3];
+                if (over & 2)
+                    v[0] = v[2], v[1] = v[3];
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            put(la, i, ar, ak, ra[i]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float col[4] = {rb[0][e], rb[1][e], rb[2][e], rb[3][e]};
+            put(lb, e, bn / 4, bk, col);
+        }
+    };
+    const int wm = wave / 2 * 2, wn = wave % 2 * 2;  // the wave's first row tile and column tile
+    floatx16 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < kNJ; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[i][j][r] = 0.f;
-
-    float ra[S::kAPer], rb[8 * kBPasses];
-    auto stash = [&](int buf) {
-        const int am = tid / S::kAThreadsPerRow, ak = (tid % S::kAThreadsPerRow) * S::kAPer;
-        const int bn = (tid % kBThreadsPerRow) * 8;
+    const int at = lane / 32 * kK8Stride + lane % 32 * 16;
+    auto multiply = [&] {
 #pragma unroll
-        for (int e = 0; e < S::kAPer; ++e)
-            As[buf][ak + e][am] = ra[e];
+        for (int kb = 0; kb < kSplitK / 16; ++kb) {
+            bf8 a[2][kParts], b[2][kParts];
 #pragma unroll
-        for (int pass = 0; pass < kBPasses; ++pass) {
-            const int bk = pass * kBRowsPerPass + tid / kBThreadsPerRow;
+            for (int s = 0; s < kParts; ++s)
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                Bs[buf][bk][bn + e] = rb[pass * 8 + e];
+                for (int i = 0; i < 2; ++i) {
+                    const int off = kb * 2 * kK8Stride + at;
+                    a[i][s] = *reinterpret_cast<const bf8 *>(la + (s * 4 + wm + i) * kTileStride + off);
+                    b[i][s] = *reinterpret_cast<const bf8 *>(lb + (s * 4 + wn + i) * kTileStride + off);
+                }
+            // the small products first
+#pragma unroll
+            for (int sum = kParts - 1; sum >= 0; --sum)
+#pragma unroll
+                for (int s = 0; s <= sum; ++s)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][s], b[j][sum - s], acc[i][j], 0,
+                                                                                0, 0);
         }
     };
-
-    fetch<TM>(g, m0, n0, 0, vec, ra, rb);
-    stash(0);
-    __syncthreads();
-    const int lrow = lane >> 5, lcol = lane & 31;
-    int buf = 0;
-    for (int k0 = 0; k0 < g.K; k0 += kTileK) {
-        const bool more = k0 + kTileK < g.K;
-        if (more)
-            fetch<TM>(g, m0, n0, k0 + kTileK, vec, ra, rb);
-        // The operands of step kk + 2 are read from LDS before step kk's products
-        // are issued (two register sets), so the LDS latency hides behind eight
-        // matrix instructions; the scheduling barrier keeps the compiler from
-        // sinking the reads back next to their use. Measured +1.5-1.9%.
-        float a[2][2], b[2][kNJ];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            a[0][i] = As[buf][lrow][wm + i * 32 + lcol];
-#pragma unroll
-        for (int j = 0; j < kNJ; ++j)
-            b[0][j] = Bs[buf][lrow][wn + j * 32 + lcol];
-#pragma unroll
-        for (int kk = 0; kk < kTileK; kk += 2) {
-            const int cur = (kk / 2) & 1, nxt = cur ^ 1;
-            if (kk + 2 < kTileK) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    a[nxt][i] = As[buf][kk + 2 + lrow][wm + i * 32 + lcol];
-#pragma unroll
-                for (int j = 0; j < kNJ; ++j)
-                    b[nxt][j] = Bs[buf][kk + 2 + lrow][wn + j * 32 + lcol];
-            }
+    if (threadIdx.x == 0)
+        redo = 0;
+    const int stages = (g.K + kSplitK - 1) / kSplitK;
+    if constexpr (GROUPS == 1) {
+        if (stages > 0)
+            fetch(0);
+        for (int p = 0; p < stages; ++p) {
+            stash();
+            lds_barrier();
+            if (p + 1 < stages)
+                fetch((p + 1) * kSplitK);
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < kNJ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[cur][i], b[cur][j], acc[i][j], 0, 0, 0);
+            multiply();
+            lds_barrier();
         }
-        if (more)
-            stash(buf ^ 1);
-        __syncthreads();
-        buf ^= 1;
+    } else {
+        // phase p: group p % 2 multiplies stage p while the other writes stage p + 1
+        if (group < stages)
+            fetch(group * kSplitK);
+        if (group == 0 && stages > 0)
+            stash();
+        lds_barrier();
+        for (int p = 0; p < stages; ++p) {
+            if (group == (p & 1)) {
+                if (p + 2 < stages)
+                    fetch((p + 2) * kSplitK);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply();
+            } else if (p + 1 < stages) {
+                stash();
+            }
+            lds_barrier();
+        }
     }
 
+    unsigned top = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < kNJ; ++j) {
-            const int col = n0 + wn + j * 32 + lcol;
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = m0 + wm + i * 32 + 8 * (r >> 2) + 4 * lrow + (r & 3);
-                if (row < g.M && col < g.N)
-                    g.C[static_cast<size_t>(row) * g.ldc + col] = acc[i][j][r];
+            for (int r = 0; r < 16; ++r)
+                top = max(top, __float_as_uint(acc[i][j][r]) & 0x7fffffffu);
+    __syncthreads();  // redo is cleared, and the stages are read
+    if (tiny < kTinyBits - 1u || top >= 0x7f800000u)
+        redo = 1;
+    __syncthreads();
+    if (redo != 0) {
+        for (int i = group; i < 2; i += GROUPS)
+            for (int j = 0; j < 2; ++j) {
+                floatx16 sum[1];
+                const int mt = m0 + (wm + i) * 32, c = n0 + 4 * (lane % 32) + wn + j;
+                direct_sum<32, 1, 4>(g, mt, n0 + wn + j, lane, 0, 1, sum);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = mt + Mfma<32>::row(lane, r);
+                    if (row < g.M && c < g.N)
+                        g.C[static_cast<size_t>(row) * g.ldc + c] = sum[0][r];
+                }
+            }
+        return;
+    }
+    // Through LDS, where the groups' sums meet, to rows of C in order: first the
+    // even 32-row tiles, then the odd ones.
+    constexpr int kHalf = kSplitTile / 2 * kSplitTile;
+    float *out = reinterpret_cast<float *>(&lds[0][0][0]);
+    static_assert(GROUPS * kHalf * sizeof(float) <= sizeof lds, "the sums fit the stages' place");
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            *reinterpret_cast<floatx2 *>(out + group * kHalf + (wm * 16 + Mfma<32>::row(lane, r)) * kSplitTile +
+                                         4 * (lane % 32) + wn) = floatx2{acc[i][0][r], acc[i][1][r]};
+        __syncthreads();
+        for (int e = threadIdx.x; e < kHalf / 4; e += 256 * GROUPS) {
+            float4u v = *reinterpret_cast<const floatx4 *>(out + 4 * e);
+            if constexpr (GROUPS == 2)
+                v += *reinterpret_cast<const floatx4 *>(out + kHalf + 4 * e);
+            const int r = e / (kSplitTile / 4), row = m0 + (r / 32 * 2 + i) * 32 + r % 32;
+            const int c = n0 + e % (kSplitTile / 4) * 4;
+            if (row < g.M) {
+                float *p = g.C + static_cast<size_t>(row) * g.ldc + c;
+                if (c + 4 <= g.N)
+                    *reinterpret_cast<float4u *>(p) = v;
+                else
+                    for (int q = 0; c + q < g.N; ++q)
+                        p[q] = v[q];
             }
         }
+        __syncthreads();
+    }
 }
 
-}  // namespace
+enum class Form { kDirect16, kDirect32x16, kDirect32, kSplit, kSplitShared };
 
-namespace {
-
-// Work-groups of a tile height resident on one CU at a time (registers and LDS
-// decide: two of the 128-row kernel, three of the 64-row one on gfx950), from
-// the runtime's occupancy query, taken once.
-template <int TM>
-int resident_per_cu() {
-    static const int n = [] {
-        int blocks = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, gemm_f32_kernel<TM>, kGemmThreads, 0) != hipSuccess ||
-            blocks < 1)
-            blocks = 1;
-        return blocks;
-    }();
-    return n;
+long long tiles(const GemmArgs &g, int tm, int tn) {
+    return static_cast<long long>((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn);
 }
 
-// Fraction of the work-group slots busy over the whole product when `tiles`
-// tiles run in rounds of `slots`: the last round's idle slots are the tail.
-double round_fill(long long tiles, long long slots) {
-    const long long rounds = (tiles + slots - 1) / slots;
-    return static_cast<double>(tiles) / static_cast<double>(rounds * slots);
+// The form with the least estimated time, in microseconds. A direct form's
+// rounds of one tile per CU take a fixed cost and a share of K each; a split one's rounds of
+// resident tiles (two groups: one per CU, and a part-filled last round is
+// faster; one group: two per CU, better at small K, where a tile's fixed cost
+// counts) a fixed cost and a share. Fitted to 46 products (M 64..8192, N 8..8192,
+// K 32..8192); on those and 50 drawn ones the choice takes 1.02 times the best
+// form's time on average, 1.36 at worst (of 4 us).
+Form pick_form(const GemmArgs &g) {
+    const double k = g.K;
+    auto direct = [&](int tm, int tn, double fixed, double share) {
+        return 3.0 - fixed + (fixed + k * share) * static_cast<double>((tiles(g, tm, tn) + kCus - 1) / kCus);
+    };
+    const long long big = tiles(g, kSplitTile, kSplitTile);
+    auto rounds = [&](int slots) { return static_cast<double>(big / slots); };
+    auto rest = [&](int slots) { return static_cast<double>(big % slots) / slots; };
+    const double alone = 5.0 + rounds(2 * kCus) * (4.1 + 0.09 * k) +
+                         (rest(2 * kCus) > 0 ? 4.1 + k * (rest(2 * kCus) > 0.5 ? 0.09 : 0.064) : 0.0);
+    const double shared =
+        5.0 + rounds(kCus) * (4.2 + 0.0442 * k) + (rest(kCus) > 0 ? 4.2 + k * (0.031 + 0.012 * rest(kCus)) : 0.0);
+    const double us[] = {direct(16, 16, 0.5, 2.7e-3), direct(32, 16, 0.3, 5.2e-3), direct(32, 32, 0.5, 6.9e-3),
+                         alone, shared};
+    int best = 0;
+    for (int f = 1; f < 5; ++f)
+        if (us[f] < us[best])
+            best = f;
+    return static_cast<Form>(best);
+}
+
+template <int BASE, int MT, int KS>
+void run_direct(const GemmArgs &g, hipStream_t s) {
+    const int tn = (g.N + BASE - 1) / BASE;
+    gemm_direct_kernel<BASE, MT, KS>
+        <<<static_cast<unsigned>(tiles(g, BASE * MT, BASE)), KS * 64, 0, s>>>(g, tn);
 }
 
 }  // namespace
@@ -251,25 +533,24 @@ double round_fill(long long tiles, long long slots) {
 void launch_gemm_f32(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc,
                      hipStream_t s) {
     const GemmArgs g{M, N, K, A, lda, B, ldb, C, ldc};
-    const bool aligned = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(B) % 16 == 0) &&
-                         lda % 4 == 0 && ldb % 4 == 0;
-    // Tile height by the tail of the last round of tiles: the 128-row tiles
-    // reuse each operand more and run about 5% faster in steady state (8192^3:
-    // 141 against 133.5 TFLOP/s), so they are taken unless the 64-row ones fill
-    // the rounds of resident work-groups better by more than that. Measured:
-    // 2048^3 104 against 61 TFLOP/s and 3072^3 99 against 79 for 64 rows,
-    // 4096^3 138 against 109 for 128 rows, and 6144^3 133 for 64 rows against
-    // 105 for 128 (1152 tiles of 128 rows are 2.25 rounds of 512).
-    const long long tiles128 = static_cast<long long>((N + kTileN - 1) / kTileN) * ((M + 127) / 128);
-    const long long tiles64 = static_cast<long long>((N + kTileN - 1) / kTileN) * ((M + 63) / 64);
-    const double fill128 = round_fill(tiles128, static_cast<long long>(kCus) * resident_per_cu<128>());
-    const double fill64 = round_fill(tiles64, static_cast<long long>(kCus) * resident_per_cu<64>());
-    if (fill128 >= 0.95 * fill64) {
-        const dim3 grid((N + kTileN - 1) / kTileN, (M + 127) / 128);
-        hipLaunchKernelGGL(gemm_f32_kernel<128>, grid, dim3(kGemmThreads), 0, s, g, aligned ? 1 : 0);
-    } else {
-        const dim3 grid((N + kTileN - 1) / kTileN, (M + 63) / 64);
-        hipLaunchKernelGGL(gemm_f32_kernel<64>, grid, dim3(kGemmThreads), 0, s, g, aligned ? 1 : 0);
+    const int tn = (N + kSplitTile - 1) / kSplitTile;
+    const unsigned big = static_cast<unsigned>(tiles(g, kSplitTile, kSplitTile));
+    switch (pick_form(g)) {
+    case Form::kDirect16:
+        run_direct<16, 1, 16>(g, s);
+        break;
+    case Form::kDirect32x16:
+        run_direct<16, 2, 8>(g, s);
+        break;
+    case Form::kDirect32:
+        run_direct<32, 1, 8>(g, s);
+        break;
+    case Form::kSplit:
+        gemm_split_kernel<1><<<big, 256, 0, s>>>(g, tn);
+        break;
+    case Form::kSplitShared:
+        gemm_split_kernel<2><<<big, 512, 0, s>>>(g, tn);
+        break;
     }
     hip_check(hipGetLastError(), "gemm kernel launch");
 }
