@@ -30,15 +30,22 @@
 //    directly (16 bytes per lane) while the current plane is computed: they need
 //    no registers on the way, of which the coefficients of two planes and two
 //    windows leave none. Each slot is refilled as soon as it has been read, so
-//    the loads in flight never drain. Narrower rows fetch without LDS; there
-//    several work-groups share a CU and overlap.
+//    the loads in flight never drain. In bfloat16 a plane is half the bytes, too
+//    few in flight for HBM's latency, and LDS holds two planes: the one after
+//    the next is fetched too (257x257x513: 245 -> 215 us per pair). Narrower rows
+//    fetch without LDS; there several work-groups share a CU and overlap.
+//  * The march alternates between two sets of registers for each window's planes
+//    and the coefficients, two planes per turn of the loop. Moving them at every
+//    plane's end took a third of the instructions: FP32 367 -> 361 us per pair,
+//    161x161x321 in one round of work-groups 89.7 -> 84.8, bfloat16 there 78.0 ->
+//    70.2 (with the deeper fetch).
 //
 // Measured at 257x257x513, an iteration as three nests against half a pair:
-// FP32 385 -> 186 us, bfloat16-offset 265 -> 125 us (as one fused sweep: 316 and
-// 188). A pair moves 1.97 GB of HBM in FP32 (1.86 the least; 5.3 TB/s) and
-// takes 357 us with its arithmetic left out: the loads bound it, and of the
-// 86% of the streaming rate that it reaches the margins' L2 reads and the fill
-// of each march are the rest.
+// FP32 385 -> 181 us, bfloat16-offset 265 -> 108 us (as one fused sweep: 316 and
+// 188). A pair moves 1.97 GB of HBM in FP32 (1.86 the least; 5.4 TB/s) and took
+// 357 us with its arithmetic left out: the loads bound it, and of the 88% of the
+// streaming rate that it reaches the margins' L2 reads and the fill of each
+// march are the rest.
 #include <algorithm>
 #include <type_traits>
 
@@ -136,18 +143,6 @@ struct Coefs {
     }
 };
 
-template <int VEC, bool BF16>
-__device__ __forceinline__ void decode(const GridView &g, const Coefs<VEC, BF16> &c, Coefs<VEC, false> &out) {
-#pragma unroll
-    for (int n = 0; n < kNCoef; ++n) {
-        float v[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e)
-            v[e] = c.get(g, n, e);
-        out.x[n] = pack<VEC>(v);
-    }
-}
-
 // Lane l receives lane l-1's (l+1's) value, lane 0 (63) `edge`.
 __device__ __forceinline__ float from_left(float v, float edge) {
     return __uint_as_float(
@@ -190,41 +185,40 @@ struct Plane {
     }
 };
 
-// Plane k-1 (c, d, dc) and plane k of a point's window.
+// What is still needed of plane k-1 when plane k is updated.
 template <int VEC>
-struct Window {
-    float zc[VEC], zd[VEC], zdc[VEC];
-    Plane<VEC> m;
-    __device__ __forceinline__ void slide(const Plane<VEC> &n) {
+struct Behind {
+    float c[VEC], d[VEC], dc[VEC];
+    __device__ __forceinline__ void keep(const Plane<VEC> &p) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-            zc[e] = m.c[e];
-            zd[e] = m.d[e];
-            zdc[e] = m.dc[e];
+            c[e] = p.c[e];
+            d[e] = p.d[e];
+            dc[e] = p.dc[e];
         }
-        m = n;
     }
 };
 
-// The sweep's update of plane k (w.m) once plane k+1 (n) is known, operation
-// for operation in the sweep's order.
+// The sweep's update of plane k (m) between planes k-1 (z) and k+1 (n),
+// operation for operation in the sweep's order.
 template <int VEC, bool BF16>
-__device__ __forceinline__ void relax(const GridView &g, const Window<VEC> &w, const Plane<VEC> &n,
-                                      const Coefs<VEC, BF16> &C, float omega, float (&out)[VEC]) {
+__device__ __forceinline__ void relax(const GridView &g, const Behind<VEC> &z, const Plane<VEC> &m,
+                                      const Plane<VEC> &n, const Coefs<VEC, BF16> &C, float omega,
+                                      float (&out)[VEC]) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        const float rt = e < VEC - 1 ? w.m.c[e + 1] : w.m.r;
-        const float lf = e > 0 ? w.m.c[e - 1] : w.m.l;
-        const float centre = w.m.c[e];
+        const float rt = e < VEC - 1 ? m.c[e + 1] : m.r;
+        const float lf = e > 0 ? m.c[e - 1] : m.l;
+        const float centre = m.c[e];
         float s0 = C.get(g, 0, e) * rt;
-        s0 = fmaf(C.get(g, 1, e), w.m.b[e], s0);
+        s0 = fmaf(C.get(g, 1, e), m.b[e], s0);
         s0 = fmaf(C.get(g, 2, e), n.c[e], s0);
-        s0 = fmaf(C.get(g, 4, e), w.m.dd[e], s0);
-        s0 = fmaf(C.get(g, 5, e), n.d[e] - w.zd[e], s0);
-        s0 = fmaf(C.get(g, 6, e), n.dc[e] - w.zdc[e], s0);
+        s0 = fmaf(C.get(g, 4, e), m.dd[e], s0);
+        s0 = fmaf(C.get(g, 5, e), n.d[e] - z.d[e], s0);
+        s0 = fmaf(C.get(g, 6, e), n.dc[e] - z.dc[e], s0);
         s0 = fmaf(C.get(g, 7, e), lf, s0);
-        s0 = fmaf(C.get(g, 8, e), w.m.a[e], s0);
-        s0 = fmaf(C.get(g, 9, e), w.zc[e], s0);
+        s0 = fmaf(C.get(g, 8, e), m.a[e], s0);
+        s0 = fmaf(C.get(g, 9, e), z.c[e], s0);
         s0 += C.get(g, 11, e);
         const float ss = fmaf(C.get(g, 3, e), s0, -centre) * C.get(g, 10, e);
         out[e] = fmaf(omega, ss, centre);
@@ -270,11 +264,12 @@ __device__ __forceinline__ double group_sum(const double *x, long long n, double
 template <int VEC, bool BF16, int W>
 struct Shared {
     static constexpr bool kDma = VEC == 4;
+    static constexpr int kDepth = kDma && BF16 ? 2 : 1;  // planes of coefficients fetched ahead
     typename VecOf<VEC>::F u[2][W * kWave];  // step 1's planes m and m-1
     double wsum[2][W];
-    // what the waves fetch ahead: the next plane's coefficients, and the rows
+    // what the waves fetch ahead: the next planes' coefficients, and the rows
     // a, c, b of the plane after it with the values beside them
-    typename Coefs<VEC, BF16>::T next[kDma ? W : 1][kDma ? kNCoef : 1][kWave];
+    typename Coefs<VEC, BF16>::T next[kDepth][kDma ? W : 1][kDma ? kNCoef : 1][kWave];
     typename VecOf<VEC>::F rows[kDma ? W : 1][kDma ? 3 : 1][kWave];
     float beside[kDma ? W : 1][kWave];
 };
@@ -290,9 +285,7 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
     typedef typename VecOf<VEC>::F F;
     typedef Coefs<VEC, BF16> C12;
     constexpr bool kDma = Shared<VEC, BF16, W>::kDma;
-    // bfloat16 is decoded once for both steps where registers allow: the flat
-    // form's lane masks leave too few.
-    constexpr bool kDecoded = kDma && !(BF16 && FLAT);
+    constexpr int kDepth = Shared<VEC, BF16, W>::kDepth;
     constexpr int S = kWave * VEC;
     constexpr int kEb = BF16 ? 2 : 4;
     const int lane = threadIdx.x & (kWave - 1);
@@ -425,9 +418,9 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
         db = 2u * static_cast<unsigned>(
                       FLAT ? coef_at(min(max(ts + wave * S + at8, 0), pitch * g.J - 8), 8) : min(ts + at8, g.cpitch - 8));
     }
-    auto dma = [&](int t, int k, auto nt) {
+    auto dma = [&](int t, int k, int slot, auto nt) {
         constexpr int kAux = decltype(nt)::value ? 2 : 0;
-        auto *dst = (OFL_LDS void *)&sh.next[wd][kDma ? t : 0][0];
+        auto *dst = (OFL_LDS void *)&sh.next[slot][wd][kDma ? t : 0][0];
         if constexpr (BF16) {
             const char *b0 = coef_base(t, k), *b1 = coef_base(t + 1, k);
             __builtin_amdgcn_global_load_lds((OFL_GLOBAL void *)((lane < 32 ? b0 : b1) + db), dst, 16, 0, kAux);
@@ -437,69 +430,80 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
     };
     constexpr int kPer = BF16 ? 2 : 1;     // coefficients per load
     constexpr int kGroup = BF16 ? 4 : 3;   // coefficients per refill step
-    auto refill = [&](int t0, int k) {
+    auto refill = [&](int t0, int k, int slot) {
         if (shared_rows) {
 #pragma unroll
             for (int t = t0; t < t0 + kGroup; t += kPer)
-                dma(t, k, std::false_type{});
+                dma(t, k, slot, std::false_type{});
         } else {
 #pragma unroll
             for (int t = t0; t < t0 + kGroup; t += kPer)
-                dma(t, k, std::true_type{});
+                dma(t, k, slot, std::true_type{});
         }
     };
-    auto take = [&](C12 &c, int t0, int n) {
+    auto take = [&](C12 &c, int t0, int n, int slot) {
 #pragma unroll
         for (int t = t0; t < t0 + n; ++t)
-            c.x[t] = sh.next[wd][kDma ? t : 0][lane];
+            c.x[t] = sh.next[slot][wd][kDma ? t : 0][lane];
     };
 
-    Window<VEC> w1, w2;
+    // Alternating register sets take an odd number of planes, the last of which
+    // is peeled: an even march starts one plane early, whose results nothing
+    // reads. Narrower forms hide the moves behind their second work-group.
+    constexpr bool kAlternate = VEC == 4;
+    const int start = m0 - 1 - (kAlternate ? (m1 - m0 + 1) & 1 : 0);
+    Plane<VEC> p1[2], p2[2];
+    Behind<VEC> z1, z2;
     Edges hm = {};
     {
-        Plane<VEC> n;
-        plane_of(load_rows(m0 - 2), n);
-        w1.m = n;
-        const Rows r = load_rows(m0 - 1);
-        plane_of(r, n);
-        w1.slide(n);
+        plane_of(load_rows(start - 1), p1[0]);
+        z1.keep(p1[0]);
+        const Rows r = load_rows(start);
+        plane_of(r, p1[0]);
         hm = spread(r.h);
     }
     Rows nr;
     if constexpr (kDma) {
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_rows(m0);
-        __builtin_amdgcn_sched_barrier(0);
+        auto coefs = [&](int m) {
 #pragma unroll
-        for (int t = 0; t < kNCoef; t += kGroup)
-            refill(t, max(m0 - 1, 1));
+            for (int t = 0; t < kNCoef; t += kGroup)
+                refill(t, min(max(m, 1), g.K - 2), (m - start) % kDepth);
+            __builtin_amdgcn_sched_barrier(0);
+        };
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kDepth == 2)
+            coefs(start);
+        fetch_rows(start + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        coefs(start + kDepth - 1);
     } else {
-        nr = load_rows(m0);
+        nr = load_rows(start + 1);
     }
 
-    Coefs<VEC, BF16 && !kDecoded> lag;  // plane m-1's coefficients
+    C12 D[2];  // a plane's coefficients, kept for its second step
     double r1 = 0.0, r2 = 0.0;
     float o[VEC];
     auto store = [&](int k) {
         if (row_out && own)
             __builtin_nontemporal_store(pack<VEC>(o), (OFL_GLOBAL F *)at<F>(g.wrk2 + k * g.plane + (FLAT ? 0 : lc), pb));
     };
-    auto step = [&](int m, auto last_plane) {
+    auto step = [&](int m, auto parity, auto last_plane) {
         constexpr bool kLast = decltype(last_plane)::value;
-        C12 C;
-        Plane<VEC> n;
+        constexpr int kThis = decltype(parity)::value, kNext = kThis ^ 1;
+        C12 &C = D[kThis];
+        Plane<VEC> &c = p1[kThis], &n = p1[kNext];
         Rows r;
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (kDma) {
-            // In flight, oldest first: the next plane's rows (4 loads), this
-            // plane's coefficients. What has landed is read and its place
-            // refilled before the next is waited for, so that always
-            // kLoads - kStep + 4 newer loads follow the awaited ones (a store
-            // among them only makes the wait stricter).
+            // In flight, oldest first (a store among them only makes a wait
+            // stricter): FP32, the next plane's rows (4 loads), this plane's
+            // coefficients; bfloat16, this plane's coefficients, the rows, the
+            // next plane's coefficients.
             constexpr int kLoads = kNCoef / kPer, kStep = kGroup / kPer;
-            __builtin_amdgcn_s_waitcnt(0x0f70 | kLoads);  // vmcnt
+            __builtin_amdgcn_s_waitcnt(0x0f70 | (kLast && kDepth == 2 ? 0 : kLoads));  // vmcnt
             r = take_rows();
+            if constexpr (kDepth == 2)
+                take(C, 0, kNCoef, kThis);
             __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): read before it is overwritten
             __builtin_amdgcn_sched_barrier(0);
             if (m > m0 + 1)
@@ -507,19 +511,29 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
             if constexpr (!kLast) {
                 fetch_rows(m + 2);
                 __builtin_amdgcn_sched_barrier(0);
-                const int k = min(m + 1, g.K - 2);
+                if constexpr (kDepth == 2) {
+                    if (m + 2 <= m1)
 #pragma unroll
-                for (int t = 0; t < kNCoef; t += kGroup) {
-                    __builtin_amdgcn_s_waitcnt(0x0f70 | (kLoads - kStep + 4));
-                    take(C, t, kGroup);
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                    __builtin_amdgcn_sched_barrier(0);
-                    refill(t, k);
-                    __builtin_amdgcn_sched_barrier(0);
+                        for (int t = 0; t < kNCoef; t += kGroup)
+                            refill(t, min(m + 2, g.K - 2), kThis);
+                } else {
+                    // What has landed is read and its place refilled before the
+                    // next is waited for, so that always kLoads - kStep + 4 newer
+                    // loads follow the awaited ones.
+                    const int k = min(m + 1, g.K - 2);
+#pragma unroll
+                    for (int t = 0; t < kNCoef; t += kGroup) {
+                        __builtin_amdgcn_s_waitcnt(0x0f70 | (kLoads - kStep + 4));
+                        take(C, t, kGroup, 0);
+                        __builtin_amdgcn_s_waitcnt(0xc07f);
+                        __builtin_amdgcn_sched_barrier(0);
+                        refill(t, k, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-            } else {
+            } else if constexpr (kDepth == 1) {
                 __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-                take(C, 0, kNCoef);
+                take(C, 0, kNCoef, 0);
             }
         } else {
             r = nr;
@@ -538,36 +552,31 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
         }
         __builtin_amdgcn_sched_barrier(0);
         plane_of(r, n);
-        Coefs<VEC, BF16 && !kDecoded> D;
-        if constexpr (BF16 && kDecoded)
-            decode<VEC, BF16>(g, C, D);
-        else
-            D = C;
         float u[VEC];
         if (active && m >= 1 && m <= g.K - 2) {
-            relax(g, w1, n, D, omega, u);
+            relax(g, z1, c, n, C, omega, u);
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
-                u[e] = in[e] ? u[e] : w1.m.c[e];
+                u[e] = in[e] ? u[e] : c.c[e];
             if (row_out && own && m >= m0 && m < m1) {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
-                    const double x = static_cast<double>(u[e] - w1.m.c[e]);
+                    const double x = static_cast<double>(u[e] - c.c[e]);
                     r1 = fma(x, x, r1);
                 }
             }
         } else {
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
-                u[e] = w1.m.c[e];
+                u[e] = c.c[e];
         }
-        w1.slide(n);
+        z1.keep(c);
         F *um = sh.u[m & 1];
         const int at_u = wave * kWave + lane;
         um[at_u] = pack<VEC>(u);
         lds_barrier();
         if (FLAT || row_out) {
-            Plane<VEC> n2;
+            Plane<VEC> &c2 = p2[kThis], &n2 = p2[kNext];
             if constexpr (FLAT) {
                 const int step = pitch / VEC, end = W * kWave - 1;
                 unpack<VEC>(um[max(at_u - step, 0)], n2.a);
@@ -584,28 +593,40 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
                 n2.c[e] = u[e];
             n2.derive(hm);
             if (m > m0) {
-                relax(g, w2, n2, lag, omega, o);
+                relax(g, z2, c2, n2, D[kNext], omega, o);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
-                    o[e] = in[e] ? o[e] : w2.m.c[e];
+                    o[e] = in[e] ? o[e] : c2.c[e];
                 if (row_out && own) {
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) {
-                        const double x = static_cast<double>(o[e] - w2.m.c[e]);
+                        const double x = static_cast<double>(o[e] - c2.c[e]);
                         r2 = fma(x, x, r2);
                     }
                 }
             }
-            w2.slide(n2);
+            z2.keep(c2);
         }
-        lag = D;
         // step 2's plane m+1 lies beside the boundary column of p's plane m+1
         if constexpr (!FLAT)
             hm = spread(r.h);
     };
-    for (int m = m0 - 1; m < m1; ++m)
-        step(m, std::false_type{});
-    step(m1, std::true_type{});
+    constexpr std::integral_constant<int, 0> kEven{};
+    constexpr std::integral_constant<int, 1> kOdd{};
+    if constexpr (kAlternate) {
+        for (int m = start; m < m1; m += 2) {
+            step(m, kEven, std::false_type{});
+            step(m + 1, kOdd, std::false_type{});
+        }
+    } else {
+        for (int m = start; m < m1; ++m) {
+            step(m, kEven, std::false_type{});
+            p1[0] = p1[1];
+            p2[0] = p2[1];
+            D[1] = D[0];
+        }
+    }
+    step(m1, kEven, std::true_type{});
     store(m1 - 1);
 #pragma unroll
     for (int d = kWave / 2; d >= 1; d >>= 1) {
@@ -629,8 +650,8 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
 // second. The last work-group of the launch instead turns the previous pair's
 // sums (prev, may be null) into gosa, iteration by iteration.
 template <int VEC, bool BF16, int W>
-__global__ __launch_bounds__(W *kWave, VEC == 4 ? 1 : 4) void pair_kernel(GridView g, PairShape s, float omega, double *parts,
-                                                        const double *prev) {
+__global__ __launch_bounds__(W *kWave, VEC == 4 ? 1 : 4) void pair_kernel(
+    GridView g, PairShape s, float omega, double *parts, const double *prev) {
     constexpr int S = kWave * VEC;
     __shared__ Shared<VEC, BF16, W> sh;
     const int blocks = s.nti * s.njt * s.nkc;

@@ -34,10 +34,12 @@ inline int pair_itiles(int I, int vec) {
 // barrier and arithmetic) and its share of the memory rate, both fitted to
 // launches of 12 grids from 33x33x65 to 385x257x385 in 30 to 60 decompositions
 // each; what the last-level cache holds (arrays of up to 224 MiB) streams twice
-// as fast. The choice is within 3% of the best measured one on 20 of the 24
-// grids and formats, 10% at worst. What it decides most is how full the last
-// round is: at 257x257x513 in FP32, 7 waves and 5 chunks make 255 work-groups
-// of one round (371 us), 8 waves 258 of two (603 us) or 473 (394 us).
+// as fast, and bfloat16 at 4 points per lane, which fetches two planes ahead,
+// faster than the narrower forms. The choice is within 3% of the best measured
+// one on 21 of the 24 grids and formats, 10% at worst. What it decides most is
+// how full the last round is: at 257x257x513 in FP32, 7 waves and 5 chunks make
+// 255 work-groups of one round (361 us), 8 waves 258 of two (603 us) or 473
+// (387 us).
 //
 // A work-group computes rows and planes beyond its own for its second step. A
 // large grid runs in pairs only where that is at most 2.2 times its points (a
@@ -49,12 +51,12 @@ inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *
         return false;  // offsets inside a plane are 32-bit byte counts
     const double points = static_cast<double>(I) * J * K;
     const double bytes = points * (12 * coef_elem + 8);
-    const double per_row = (coef_elem == 4 ? 1.0e-4 : 0.52e-4) * (bytes < 224.0 * (1 << 20) ? 1.0 : 2.0);
+    const double beyond_cache = bytes < 224.0 * (1 << 20) ? 1.0 : 2.0;
     // points per lane, waves, us per plane besides its loads
     constexpr struct {
         int vec, waves;
         double fixed;
-    } kForms[] = {{4, 8, 1.54}, {4, 7, 1.39}, {2, 8, 1.23}, {1, 8, 0.74}};
+    } kForms[] = {{4, 8, 1.54}, {4, 7, 1.42}, {2, 8, 1.20}, {1, 8, 0.74}};
     double best_us = 0.0;
     best->vec = 0;
     for (const auto &form : kForms) {
@@ -70,6 +72,8 @@ inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *
         // rows of 64 points that a work-group loads per plane (80 more points
         // for a tile boundary: the overlap and the lines it splits)
         const double rows = s.waves * (I + 80.0 * (s.nti - 1)) / s.nti / kWave;
+        const double per_row =
+            (coef_elem == 4 ? 1.0e-4 : (s.vec == 4 ? 0.48e-4 : 0.66e-4)) * beyond_cache;
         for (int nkc = 1; nkc <= std::min(K - 2, 1024) && tiles * nkc <= 8192; ++nkc) {
             const int chunk = (K - 2 + nkc - 1) / nkc;
             if (chunk == s.chunk)
