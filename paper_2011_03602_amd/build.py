@@ -20,7 +20,7 @@ BUILD = os.path.join(ROOT, "_build", "ofl")
 LIB = os.path.join(HERE, "libofl.so")
 ARCH = "gfx950"
 
-SOURCES = ["kernels.hip", "pair.hip", "gemm.hip", "grid.cpp", "cpu_nests.cpp", "batch.cpp", "tune.cpp", "blocks.cpp", "trace.cpp", "device.cpp"]
+SOURCES = ["kernels.hip", "pair.hip", "readback.hip", "gemm.hip", "grid.cpp", "cpu_nests.cpp", "batch.cpp", "tune.cpp", "blocks.cpp", "trace.cpp", "device.cpp"]
 
 COMMON = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

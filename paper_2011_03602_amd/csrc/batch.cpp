@@ -17,6 +17,7 @@
 
 #include "abi_util.hpp"
 #include "batch.hpp"
+#include "readback.hpp"
 
 namespace ofl {
 
@@ -53,6 +54,9 @@ void free_tables(ofl_batch *b) {
     free_dev(b->d_prange);
     free_dev(b->d_pparts);
     b->p_cnt = 0;
+    if (b->slots)
+        host_slots_free(b->slots);
+    b->slots = nullptr;
     b->tables_ready = false;
 }
 
@@ -383,6 +387,8 @@ void batch_build_tables(ofl_batch *b) {
         hip_check(hipMalloc(&b->d_pparts, 4 * sizeof(double) * pitems.size()), "hipMalloc(batch pair partials)");
         b->p_cnt = static_cast<int>(pitems.size());
     }
+    if (host_slots_alloc != nullptr)
+        b->slots = host_slots_alloc(n);
     hip_check(hipStreamSynchronize(s), "hipStreamSynchronize(batch tables)");
     b->tables_ready = true;
 }
@@ -555,6 +561,10 @@ void batch_after_run(ofl_batch *b, int iters) {
 }
 
 void batch_finish(ofl_batch *b, int iters, double *gosa_out) {
+    // every residual in one kernel behind the iterations, or a copy each
+    if (b->slots)
+        launch_publish_batch(static_cast<const GridView *>(b->d_views), static_cast<int>(b->grids.size()), b->slots,
+                             b->stream);
     hip_check(hipStreamSynchronize(b->stream), "hipStreamSynchronize(batch)");
     batch_after_run(b, iters);
     batch_mark_done(b, iters);
@@ -565,11 +575,16 @@ void batch_finish(ofl_batch *b, int iters, double *gosa_out) {
             plan_sync_host(iters, g->valid, xs);
             grid_exec(g, xs);
         }
-        hip_check(hipMemcpyAsync(&g->gosa_host, g->view.gosa, sizeof(double), hipMemcpyDeviceToHost, g->stream),
-                  "hipMemcpyAsync(gosa)");
+        if (b->slots) {
+            g->gosa_host = b->slots[t];
+        } else {
+            hip_check(hipMemcpyAsync(&g->gosa_host, g->view.gosa, sizeof(double), hipMemcpyDeviceToHost, g->stream),
+                      "hipMemcpyAsync(gosa)");
+            g->pending = true;
+        }
         g->gosa_on_dev = false;
-        g->pending = true;
-        grid_sync(g);
+        if (g->pending)
+            grid_sync(g);
         if (gosa_out)
             gosa_out[t] = g->gosa_host;
     }

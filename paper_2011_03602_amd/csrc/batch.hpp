@@ -38,6 +38,8 @@ struct ofl_batch {
     void *d_pparts = nullptr;  // two buffers of two partial sums per item
     int p_cnt = 0;
 
+    double *slots = nullptr;  // pinned host memory for every grid's residual (readback.hip)
+
     std::vector<unsigned> epochs;   // per grid, its exchanges of p and wrk2 when the views were uploaded
 
     std::vector<int> gvec;          // per grid, its points per lane in the batch

@@ -51,6 +51,7 @@ struct ofl_grid {
 
     bool gosa_on_dev = false;
     double gosa_host = 0.0;
+    double *gosa_slot = nullptr;  // pinned host memory a kernel writes gosa to (readback.hip)
 
     ofl_stats stats{};
     bool profiling = false;
