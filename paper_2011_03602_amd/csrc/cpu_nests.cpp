@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <thread>
 #include <vector>
 
@@ -158,13 +159,77 @@ void cpu_copyback(int I, int J, int K, const float *wrk2, float *p) {
     });
 }
 
-void cpu_encode_bf16(const float *x, size_t n, float bias, uint16_t *q) {
-    const int nt = static_cast<int>(std::max<size_t>(1, std::min<size_t>(static_cast<size_t>(cpu_threads()), n / 65536 + 1)));
-    parallel_planes(0, nt, static_cast<long long>(n / static_cast<size_t>(nt)), [&](int t) {
-        const size_t a = n * static_cast<size_t>(t) / static_cast<size_t>(nt);
-        const size_t b = n * static_cast<size_t>(t + 1) / static_cast<size_t>(nt);
-        for (size_t u = a; u < b; ++u)
-            q[u] = f32_to_bf16_rne(x[u] - bias);
+namespace {
+
+// The least and the greatest of x (NaN apart) and the OR of all bits, over lanes
+// of their own, so that the compiler can vectorise the loop.
+struct Range {
+    float lo = std::numeric_limits<float>::infinity(), hi = -std::numeric_limits<float>::infinity();
+    uint32_t bits = 0;
+
+    void add(const Range &r) {
+        lo = r.lo < lo ? r.lo : lo;
+        hi = r.hi > hi ? r.hi : hi;
+        bits |= r.bits;
+    }
+};
+
+Range range_of(const float *x, size_t n) {
+    constexpr int kLanes = 16;
+    float lo[kLanes], hi[kLanes];
+    uint32_t bits[kLanes] = {};
+    Range r;
+    std::fill_n(lo, kLanes, r.lo);
+    std::fill_n(hi, kLanes, r.hi);
+    for (size_t t = 0; t + kLanes <= n; t += kLanes)
+        for (int l = 0; l < kLanes; ++l) {
+            const float v = x[t + static_cast<size_t>(l)];
+            uint32_t u;
+            std::memcpy(&u, &v, sizeof u);
+            lo[l] = v < lo[l] ? v : lo[l];
+            hi[l] = v > hi[l] ? v : hi[l];
+            bits[l] |= u;
+        }
+    for (int l = 0; l < kLanes; ++l)
+        r.add({lo[l], hi[l], bits[l]});
+    for (size_t t = n / kLanes * kLanes; t < n; ++t) {
+        uint32_t u;
+        std::memcpy(&u, &x[t], sizeof u);
+        r.add({x[t], x[t], u});
+    }
+    return r;
+}
+
+}  // namespace
+
+// All arrays at once, in slices over the host threads: twelve arrays of
+// 129x129x257 on 8 threads 132 -> 10 ms with a bias, 7 ms without (one array
+// after the other, with the range scanned by one thread).
+void cpu_encode_bf16(const float *const *x, int arrays, size_t n, bool offset, float *bias, uint16_t *const *q) {
+    const int slices = static_cast<int>(std::min<size_t>(8, n / 65536 + 1));
+    const long long work = static_cast<long long>(n / static_cast<size_t>(slices));
+    auto begin = [&](int s) { return n * static_cast<size_t>(s) / static_cast<size_t>(slices); };
+    std::fill_n(bias, arrays, 0.f);
+    if (offset) {
+        std::vector<Range> part(static_cast<size_t>(arrays * slices));
+        parallel_planes(0, arrays * slices, work, [&](int t) {
+            const size_t a = begin(t % slices), b = begin(t % slices + 1);
+            part[static_cast<size_t>(t)] = range_of(x[t / slices] + a, b - a);
+        });
+        for (int t = 0; t < arrays; ++t) {
+            Range r;
+            for (int s = 0; s < slices; ++s)
+                r.add(part[static_cast<size_t>(t * slices + s)]);
+            if ((r.bits & 0xffffu) != 0)
+                bias[t] = static_cast<float>(0.5 * (static_cast<double>(r.lo) + static_cast<double>(r.hi)));
+        }
+    }
+    parallel_planes(0, arrays * slices, work, [&](int t) {
+        const float *src = x[t / slices];
+        uint16_t *dst = q[t / slices];
+        const float b = bias[t / slices];
+        for (size_t u = begin(t % slices), end = begin(t % slices + 1); u < end; ++u)
+            dst[u] = f32_to_bf16_rne(src[u] - b);
     });
 }
 

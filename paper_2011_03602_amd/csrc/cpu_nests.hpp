@@ -14,8 +14,10 @@ void cpu_sweep_bf16(int I, int J, int K, const uint16_t *const coef[12], const f
                     float *wrk2, float omega);
 double cpu_residual(int I, int J, int K, const float *p, const float *wrk2, float omega);
 void cpu_copyback(int I, int J, int K, const float *wrk2, float *p);
-// q[t] = bfloat16(fl32(x[t] - bias)), round to nearest even.
-void cpu_encode_bf16(const float *x, size_t n, float bias, uint16_t *q);
+// q[a][t] = bfloat16(fl32(x[a][t] - bias[a])), round to nearest even, for arrays of
+// n values; bias: 0, or with `offset` the middle of the array's range where
+// bfloat16 does not hold the array exactly.
+void cpu_encode_bf16(const float *const *x, int arrays, size_t n, bool offset, float *bias, uint16_t *const *q);
 int cpu_threads();
 
 }  // namespace ofl

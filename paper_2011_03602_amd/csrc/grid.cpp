@@ -270,7 +270,7 @@ size_t array_elem_bytes(const ofl_grid *g, int a) { return (a < kNCoef && g->fmt
 const void *host_src(const ofl_grid *g, int a) {
     if (a < kNCoef)
         return g->fmt == OFL_COEF_F32 ? static_cast<const void *>(g->coef[a])
-                                       : static_cast<const void *>(g->enc[a].data());
+                                       : static_cast<const void *>(g->enc[a].get());
     return a == OFL_ARR_P ? g->p : g->wrk2;
 }
 
@@ -518,7 +518,7 @@ void cpu_nest(ofl_grid *g, int nest, float omega) {
         } else {
             const uint16_t *enc[kNCoef];
             for (int a = 0; a < kNCoef; ++a)
-                enc[a] = g->enc[a].data();
+                enc[a] = g->enc[a].get();
             cpu_sweep_bf16(g->I, g->J, g->K, enc, g->bias, g->p, g->wrk2, omega);
         }
     } else if (nest == kR) {
@@ -1021,28 +1021,12 @@ double grid_fetch_gosa(ofl_grid *g) {
 namespace {
 
 void encode_bf16(ofl_grid *g) {
+    uint16_t *enc[kNCoef];
     for (int a = 0; a < kNCoef; ++a) {
-        const float *x = g->coef[a];
-        const size_t n = g->n;
-        float lo = std::numeric_limits<float>::infinity();
-        float hi = -lo;
-        bool exact = true;
-        for (size_t t = 0; t < n; ++t) {
-            const float v = x[t];
-            lo = std::min(lo, v);
-            hi = std::max(hi, v);
-            uint32_t u;
-            std::memcpy(&u, &v, sizeof u);
-            if ((u & 0xffffu) != 0)
-                exact = false;
-        }
-        float b = 0.f;
-        if (g->fmt == OFL_COEF_BF16_OFFSET && !exact)
-            b = static_cast<float>(0.5 * (static_cast<double>(lo) + static_cast<double>(hi)));
-        g->bias[a] = b;
-        g->enc[a].resize(n);
-        cpu_encode_bf16(x, n, b, g->enc[a].data());
+        g->enc[a].reset(new uint16_t[g->n]);
+        enc[a] = g->enc[a].get();
     }
+    cpu_encode_bf16(g->coef, kNCoef, g->n, g->fmt == OFL_COEF_BF16_OFFSET, g->bias, enc);
 }
 
 }  // namespace

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -35,7 +36,7 @@ struct ofl_grid {
     ofl::Validity valid = ofl::fresh_validity();
 
     // bfloat16 formats: encoded host copies of the read-only arrays + biases
-    std::vector<uint16_t> enc[ofl::kNCoef];
+    std::unique_ptr<uint16_t[]> enc[ofl::kNCoef];
     float bias[ofl::kNCoef] = {};
 
     // device side (created on first GPU use)
