@@ -220,9 +220,12 @@ namespace {
 // Items run in rounds of one work-group per CU, each chunk + 3 planes long (two
 // margin planes and the fill of the pipeline); the chunk is the one with the
 // fewest plane steps in all. Rows so long that their margins take more than 45%
-// of a work-group's points, and batches whose margins and idle lanes exceed 2.5
-// times their points (slabs and tiny grids, unless the whole batch is small and
-// bound by its launches) stay with single iterations.
+// of a work-group's points stay with single iterations, and so does a batch whose
+// plane steps (us per plane as fitted for single grids at this width) would take
+// longer than two fused iterations at the copy rate. On 16 batches of 1 to 4
+// grids from 33x33x65 to 160x160x320 pairs were 2.1 to 6 times as fast as two
+// single iterations, also where margins and idle lanes are several times the
+// points: 65x65x129 alone 49 -> 14 us, three of them 74 -> 26.
 std::vector<PairItem> pair_items(const ofl_batch *b, std::vector<int> *range) {
     const int n = static_cast<int>(b->grids.size());
     std::vector<PairItem> items;
@@ -243,23 +246,23 @@ std::vector<PairItem> pair_items(const ofl_batch *b, std::vector<int> *range) {
         kmax = std::max(kmax, q->K - 2);
     }
     int best = 0;
-    double best_cost = 0.0, best_work = 0.0;
+    double best_cost = 0.0;
     for (int chunk = 1; chunk <= kmax; ++chunk) {
-        double count = 0.0, work = 0.0;
+        double count = 0.0;
         for (int g = 0; g < n; ++g) {
             const int planes = b->grids[static_cast<size_t>(g)]->K - 2;
             const int parts = (planes + chunk - 1) / chunk;
             count += static_cast<double>(parts) * segs[static_cast<size_t>(g)];
-            work += (planes + 2.0 * parts) * segs[static_cast<size_t>(g)] * (4 * kWave * kPairBatchWaves);
         }
         const double cost = std::ceil(count / b->cu_count) * (chunk + 3);
         if (best == 0 || cost < best_cost) {
             best = chunk;
             best_cost = cost;
-            best_work = work;
         }
     }
-    if (best_work > 2.5 * points && points * (b->fmt == OFL_COEF_F32 ? 56 : 32) > 16e6)
+    const double bytes = points * (b->fmt == OFL_COEF_F32 ? 56 : 32);
+    const double plane_us = 1.54 + (b->fmt == OFL_COEF_F32 ? 0.82 : 0.39) * (bytes < 224.0 * (1 << 20) ? 1.0 : 2.0);
+    if (best_cost * plane_us > 2.0 * (8.0 + bytes / 5.2e6))
         return items;
     for (int g = 0; g < n; ++g) {
         const ofl_grid *q = b->grids[static_cast<size_t>(g)];
