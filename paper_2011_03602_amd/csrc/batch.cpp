@@ -242,7 +242,7 @@ std::vector<PairItem> pair_items(const ofl_batch *b, std::vector<int> *range) {
             static_cast<long long>(pitch) * q->J > (1LL << 28))
             return items;
         segs[static_cast<size_t>(g)] = pair_flat_segments(q->J, pitch);
-        points += static_cast<double>(q->I - 2) * (q->J - 2) * (q->K - 2);
+        points += static_cast<double>(pitch) * q->J * q->K;  // whole rows stream
         kmax = std::max(kmax, q->K - 2);
     }
     int best = 0;

@@ -673,7 +673,7 @@ bool pair_eligible(ofl_grid *g, int iters) {
         return false;
     if (!g->pair_planned) {
         const int pitch = round_up(g->I, g->row_align > 0 ? g->row_align : kPitchAlign);
-        if (!pair_plan(g->I, g->J, g->K, pitch, g->fmt == OFL_COEF_F32 ? 4 : 2, &g->pair))
+        if (!pair_choose(g->I, g->J, g->K, pitch, g->fmt == OFL_COEF_F32 ? 4 : 2, &g->pair))
             g->pair.vec = 0;
         g->pair_planned = true;
     }

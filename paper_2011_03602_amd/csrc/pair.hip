@@ -18,9 +18,9 @@
 //    them (work-groups of one XCD are neighbours), the rest non-temporally.
 //  * Row form: a wave owns 64*VEC points of one row; rows 0 and W-1 of the
 //    work-group are the margin in j, and tiles of long rows overlap by the
-//    margin in i. Flat form (compact rows): the work-group owns 256*W consecutive
-//    points of a plane across row ends, the margin is a row and four points at
-//    each end, and no lane idles on short rows.
+//    margin in i. Flat form (batches, and rows that tiles fit badly): the
+//    work-group covers 256*W consecutive points of a plane across row ends, the
+//    margin is a row and a point at each end, and no lane idles on short rows.
 //  * The stencil is kept per plane as rows a, c, b (j-1, j, j+1), d = b - a and
 //    the right-minus-left differences of c and d: the corner sums of the sweep
 //    are differences of these, so every point gets the sweep's own operations
@@ -675,6 +675,28 @@ __global__ __launch_bounds__(W *kWave, VEC == 4 ? 1 : 4) void pair_kernel(
                                     min(m0 + s.chunk, g.K - 1), omega, parts + blockIdx.x, blocks);
 }
 
+// One grid in flat form: s.nti segments of a plane, s.nkc chunks.
+template <bool BF16, int W>
+__global__ __launch_bounds__(W *kWave) void pair_flat_kernel(GridView g, PairShape s, float omega, double *parts,
+                                                             const double *prev) {
+    __shared__ Shared<4, BF16, W> sh;
+    const int blocks = s.nti * s.nkc;
+    if (static_cast<int>(blockIdx.x) == blocks) {
+        if (prev)
+            for (int q = 0; q < 2; ++q) {
+                const double t = group_sum<W>(prev + q * blocks, blocks, sh.wsum[0]);
+                if (threadIdx.x == 0)
+                    *g.gosa = t / (static_cast<double>(omega) * static_cast<double>(omega));
+            }
+        return;
+    }
+    const int L = xcd_range(blockIdx.x, blocks);
+    const int own = pair_flat_own(g.pitch, W), first = pair_flat_first(g.pitch) + L % s.nti * own;
+    const int m0 = 1 + L / s.nti * s.chunk;
+    pair_march<4, BF16, W, true>(g, sh, first - pair_flat_margin(g.pitch), 0, first, first + own, m0,
+                                 min(m0 + s.chunk, g.K - 1), omega, parts + blockIdx.x, blocks);
+}
+
 template <int W>
 __global__ __launch_bounds__(W *kWave) void pair_fold_kernel(const double *parts, int n, double omega, double *gosa) {
     __shared__ double wsum[W];
@@ -745,7 +767,16 @@ void by_format(const GridView &g, int bf16, const PairShape &s, float omega, dou
 
 void launch_pair(const GridView &g, int bf16, const PairShape &s, float omega, double *parts, const double *prev,
                  hipStream_t st) {
-    if (s.vec == 4 && s.waves == 8)
+    if (s.flat && s.vec == 4 && s.waves == kPairBatchWaves && s.njt == 1) {
+        if (bf16)
+            pair_flat_kernel<true, kPairBatchWaves>
+                <<<s.blocks() + 1, kPairBatchWaves * kWave, 0, st>>>(g, s, omega, parts, prev);
+        else
+            pair_flat_kernel<false, kPairBatchWaves>
+                <<<s.blocks() + 1, kPairBatchWaves * kWave, 0, st>>>(g, s, omega, parts, prev);
+    } else if (s.flat)
+        fail(OFL_EINVAL, "pair sweep: no such flat shape");
+    else if (s.vec == 4 && s.waves == 8)
         by_format<4, 8>(g, bf16, s, omega, parts, prev, st);
     else if (s.vec == 4 && s.waves == 7)
         by_format<4, 7>(g, bf16, s, omega, parts, prev, st);

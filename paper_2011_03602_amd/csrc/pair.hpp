@@ -17,6 +17,7 @@ __host__ __device__ inline constexpr int pair_margin(int vec) { return vec < 2 ?
 struct PairShape {
     int vec = 0, waves = 0;
     int nti = 0, njt = 0, nkc = 0, chunk = 0;
+    bool flat = false;  // nti segments of a plane instead of tiles and rows (njt 1)
     int blocks() const { return nti * njt * nkc; }
 };
 
@@ -25,38 +26,40 @@ inline int pair_itiles(int I, int vec) {
     return I - 1 <= span ? 1 : 1 + (I - 1 - span + stride - 1) / stride;
 }
 
-// The decomposition a grid's iterations run in pairs with; false where they run
-// one by one.
-//
-// A launch is a few rounds of resident work-groups (one per CU at 4 points per
-// lane, whose registers fill it, two below). A round costs chunk + 3 planes (two
-// margin planes, and the fill of the pipeline), a plane a fixed part (its
-// barrier and arithmetic) and its share of the memory rate, both fitted to
-// launches of 12 grids from 33x33x65 to 385x257x385 in 30 to 60 decompositions
-// each; what the last-level cache holds (arrays of up to 224 MiB) streams twice
-// as fast, and bfloat16 at 4 points per lane, which fetches two planes ahead,
-// faster than the narrower forms. The choice is within 3% of the best measured
-// one on 21 of the 24 grids and formats, 10% at worst. What it decides most is
-// how full the last round is: at 257x257x513 in FP32, 7 waves and 5 chunks make
-// 255 work-groups of one round (361 us), 8 waves 258 of two (603 us) or 473
-// (387 us).
-//
-// A work-group computes rows and planes beyond its own for its second step. A
-// large grid runs in pairs only where that is at most 2.2 times its points (a
-// slab of a few rows would spend more on them than the pair saves); a small
-// one, bound by its launches, always does: 33x33x65 14.0 -> 3.1 us per
-// iteration.
-inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *best) {
+// What a pair takes in `blocks` work-groups of a form, us. A launch is a few rounds
+// of resident work-groups: one per CU at 4 points per lane, whose registers fill
+// it, two below, where one alone is faster. A round costs chunk + 3 planes (two
+// margin planes, and the fill of the pipeline), a plane a fixed part (its barrier
+// and arithmetic) and its share of the memory rate, by the rows of 64 points it
+// loads; what the last-level cache holds (arrays of up to 224 MiB) streams twice
+// as fast. Fitted to 51 grids from 33x33x65 to 385x257x385 in both formats and
+// 30 to 80 decompositions each: the choice by it takes 1.015 times the best
+// measured one on average, 1.13 at worst.
+struct PairForm {
+    int vec, waves;
+    double plane_us;
+};
+inline double pair_us(const PairForm &form, long long blocks, int chunk, double rows, double bytes, int coef_elem) {
+    const long long slots = 256 * (form.vec == 4 ? 1 : 2);
+    const double per_row = (coef_elem == 4 ? 1.18e-4 : 0.61e-4) * (bytes < 224.0 * (1 << 20) ? 1.0 : 2.0);
+    double us = 3.0 + 0.004 * static_cast<double>(blocks);
+    for (long long left = blocks; left > 0; left -= slots) {
+        const double alone = form.vec < 4 && left <= 256 ? 0.76 : 1.0;
+        us += (chunk + 3) * (form.plane_us * alone + static_cast<double>(std::min(left, slots)) * rows * per_row);
+    }
+    return us;
+}
+
+// The best decomposition of a grid's pairs by rows; false where there is none.
+// What it decides most is how full the last round is: at 257x257x513 in FP32, 7
+// waves and 5 chunks make 255 work-groups of one round (361 us), 8 waves 258 of
+// two (603 us) or 473 (387 us).
+inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *best, double *predicted_us = nullptr) {
     if (static_cast<long long>(pitch) * J > (1LL << 28))
         return false;  // offsets inside a plane are 32-bit byte counts
     const double points = static_cast<double>(I) * J * K;
     const double bytes = points * (12 * coef_elem + 8);
-    const double beyond_cache = bytes < 224.0 * (1 << 20) ? 1.0 : 2.0;
-    // points per lane, waves, us per plane besides its loads
-    constexpr struct {
-        int vec, waves;
-        double fixed;
-    } kForms[] = {{4, 8, 1.54}, {4, 7, 1.42}, {2, 8, 1.20}, {1, 8, 0.74}};
+    constexpr PairForm kForms[] = {{4, 8, 1.66}, {4, 7, 1.54}, {2, 8, 1.40}, {1, 8, 0.86}};
     double best_us = 0.0;
     best->vec = 0;
     for (const auto &form : kForms) {
@@ -67,13 +70,10 @@ inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *
         s.waves = form.waves;
         s.nti = pair_itiles(I, s.vec);
         s.njt = (J - 2 + s.waves - 3) / (s.waves - 2);
-        const long long slots = 256 * (s.vec == 4 ? 1 : 2);
         const long long tiles = static_cast<long long>(s.nti) * s.njt;
         // rows of 64 points that a work-group loads per plane (80 more points
         // for a tile boundary: the overlap and the lines it splits)
         const double rows = s.waves * (I + 80.0 * (s.nti - 1)) / s.nti / kWave;
-        const double per_row =
-            (coef_elem == 4 ? 1.0e-4 : (s.vec == 4 ? 0.48e-4 : 0.66e-4)) * beyond_cache;
         for (int nkc = 1; nkc <= std::min(K - 2, 1024) && tiles * nkc <= 8192; ++nkc) {
             const int chunk = (K - 2 + nkc - 1) / nkc;
             if (chunk == s.chunk)
@@ -83,34 +83,73 @@ inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *
             // the partial sums live in the grid's staging buffer
             if (32.0 * s.blocks() > 4.0 * points)
                 continue;
-            const double work = static_cast<double>(s.blocks()) * s.waves * (chunk + 2);
-            if (bytes > 16e6 && work > 2.2 * s.nti * (J - 2.0) * (K - 2.0))
-                continue;
-            double us = 3.0 + 0.004 * s.blocks();
-            for (long long left = s.blocks(); left > 0; left -= slots)
-                us += (chunk + 3) * (form.fixed + std::min(left, slots) * rows * per_row);
+            const double us = pair_us(form, s.blocks(), chunk, rows, bytes, coef_elem);
             if (best->vec == 0 || us < best_us) {
                 best_us = us;
                 *best = s;
             }
         }
     }
+    if (predicted_us)
+        *predicted_us = best_us;
     return best->vec != 0;
 }
 
-// Flat form, for a batch's grids: a work-group covers 256 * kPairBatchWaves
-// consecutive points of a plane, whatever the row length, and owns those that
-// lie a row and a point from either end (in whole 16-byte loads of bfloat16).
+// Flat form, for a batch's grids and single ones (pair_choose): a work-group
+// covers 256 * kPairBatchWaves consecutive points of a plane, whatever the row
+// length, and owns those that lie a row and a point from either end (in whole
+// 16-byte loads of bfloat16).
 constexpr int kPairBatchWaves = 8;
 __host__ __device__ inline constexpr int pair_flat_margin(int pitch) { return (pitch + 1 + 7) / 8 * 8; }
 __host__ __device__ inline constexpr int pair_flat_own(int pitch, int waves) {
     return waves * kWave * 4 - 2 * pair_flat_margin(pitch);
 }
 // The first owned point of a plane's first work-group, and how many there are.
-inline int pair_flat_first(int pitch) { return pitch / 8 * 8; }
+__host__ __device__ inline constexpr int pair_flat_first(int pitch) { return pitch / 8 * 8; }
 inline int pair_flat_segments(int J, int pitch) {
     const int own = pair_flat_own(pitch, kPairBatchWaves);
     return ((J - 1) * pitch - pair_flat_first(pitch) + own - 1) / own;
+}
+
+// The decomposition a single grid's iterations run in pairs with: pair_plan's, or
+// flat segments where they take less; false where the iterations run one by one.
+// Flat wins where tiles of 64, 128 or 256 points leave many lanes idle or cut
+// rows in pieces, us per pair: 150x150x150 FP32 44.9 -> 38.3, bfloat16 39.0 ->
+// 30.1; 161x161x321 85.0 -> 79.5 and 71.2 -> 62.8; 301x99x143 49.3 -> 46.7 and
+// 39.8 -> 36.4. Pairs are worth it while they take less than two single fused
+// iterations at the copy rate (a slab of one row, whose margins are five sixths
+// of the work, may not); 33x33x65 14.0 -> 3.1 us per iteration.
+inline bool pair_choose(int I, int J, int K, int pitch, int coef_elem, PairShape *best) {
+    double us = 0.0;
+    if (!pair_plan(I, J, K, pitch, coef_elem, best, &us))
+        return false;
+    const double points = static_cast<double>(I) * J * K;
+    const double bytes = points * (12 * coef_elem + 8);
+    const double single_us = 2.0 * (6.0 + bytes / I * pitch / 5.2e6);  // whole rows stream
+    if (pair_flat_own(pitch, kPairBatchWaves) < 0.5 * 4 * kWave * kPairBatchWaves)
+        return us <= single_us;
+    constexpr PairForm kFlat = {4, kPairBatchWaves, 1.59};
+    PairShape s;
+    s.flat = true;
+    s.vec = 4;
+    s.waves = kPairBatchWaves;
+    s.nti = pair_flat_segments(J, pitch);
+    s.njt = 1;
+    for (int nkc = 1; nkc <= std::min(K - 2, 1024) && static_cast<long long>(s.nti) * nkc <= 8192; ++nkc) {
+        const int chunk = (K - 2 + nkc - 1) / nkc;
+        if (chunk == s.chunk)
+            continue;
+        s.chunk = chunk;
+        s.nkc = (K - 2 + chunk - 1) / chunk;
+        if (32.0 * s.blocks() > 4.0 * points)
+            continue;
+        const double t = pair_us(kFlat, s.blocks(), chunk, 4.0 * kPairBatchWaves, bytes, coef_elem);
+        if (t < us) {
+            us = t;
+            *best = s;
+        }
+    }
+    return us <= single_us;
 }
 
 // A work-group's share of a batch: grid, first owned point, planes [m0, m1).

@@ -99,6 +99,21 @@ def test_pairs_replay_and_continue():
     two.close()
 
 
+# Sizes at which single grids take flat segments: one and several per plane,
+# chunks of one and of several planes, pitches on and off multiples of 8.
+@pytest.mark.parametrize("shape", [(161, 40, 45), (150, 70, 65), (97, 40, 80), (301, 40, 46), (130, 67, 61)])
+@pytest.mark.parametrize("fmt", [ofl.OFL_COEF_F32, ofl.OFL_COEF_BF16_OFFSET])
+@pytest.mark.parametrize("row_align", [0, 4])
+def test_flat_pairs_equal_single_iterations(shape, fmt, row_align):
+    say("flat pairs", shape, "format", fmt, "row_align", row_align)
+    a = synth.make_problem(*shape, seed=31)
+    for iters in ([3], [6, 5]):
+        p1, g1 = run(a, fmt, iters, True, row_align=row_align)
+        p2, g2 = run(a, fmt, iters, False, row_align=row_align)
+        assert np.array_equal(p1, p2)
+        assert g1 == g2
+
+
 # ------------------------------------------------------------------ batches
 
 

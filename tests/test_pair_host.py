@@ -27,3 +27,13 @@ def test_device_errors_are_sticky_and_leak_nothing_in_pairs():
         res = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=600)
         assert res.returncode == 0, res.stdout + res.stderr
         assert "device-error paths ok" in res.stdout
+
+
+@needs_toolchain
+def test_flat_segments_cover_every_grid_they_are_chosen_for():
+    with tempfile.TemporaryDirectory() as d:
+        exe = os.path.join(d, "flat")
+        subprocess.run(["g++", "-std=c++17", *FLAGS, "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", f"-I{ROOT}/include",
+                        f"-I{CSRC}", os.path.join(TESTS_CSRC, "pair_flat_check.cpp"), "-o", exe], check=True)
+        res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+        assert res.returncode == 0 and "flat choices ok" in res.stdout, res.stdout + res.stderr
