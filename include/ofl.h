@@ -200,7 +200,8 @@ int ofl_jacobi_run(ofl_grid *g, int iters, float omega, double *gosa_out);
 
 /* ofl_jacobi_run for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): it
- * calls no hipMalloc, hipFree, event or graph creation. It runs the fused
+ * calls no hipMalloc, hipFree, event or graph creation. The iterations before
+ * the last go two per launch as in ofl_jacobi_run; the others are the fused
  * iteration (see ofl_set_fusion) with the sweep's per-wave residual partials
  * (two buffers: even and odd iterations) in a library-owned device array of
  * 2^19 FP64 slots (4 MiB per device, held until the process ends) instead of a
@@ -217,7 +218,8 @@ int ofl_jacobi_run(ofl_grid *g, int iters, float omega, double *gosa_out);
 int ofl_jacobi_run_static(ofl_grid *g, int iters, float omega, double *gosa_out);
 
 /* Residual of the current iterate without changing it: S with omega = 1 into
- * wrk2, then R; no copy-back. Uses the devices of the current mask. The paper
+ * wrk2, then R (as one kernel where sums are FP64, both nests are whole on the
+ * GPU with hoisted transfers and no tile is set); no copy-back. Uses the devices of the current mask. The paper
  * defines no such call: it is the offloaded program's own residual nest, run
  * once on the current iterate, for a caller that wants a convergence check
  * outside the iteration loop. */
@@ -397,7 +399,11 @@ typedef struct ofl_batch ofl_batch;
  * XCD receives runs of consecutive lines (which share halo rows). A grid created
  * with a compact desc.row_align whose rows fill few of a wave's lanes runs in
  * packed rows: each wave covers 64 * vec consecutive points of a plane across
- * row ends. EINVAL for n < 1, NULL grids, mixed devices or formats. */
+ * row ends. While no tile is set or searched, the iterations before a run's
+ * last go two per launch for all grids (as in ofl_jacobi_run), each work-group
+ * covering consecutive points of a plane across row ends; the tile is that of
+ * the remaining single iterations. EINVAL for n < 1, NULL grids, mixed devices
+ * or formats. */
 int ofl_batch_create(ofl_grid *const *grids, int n, const ofl_tile *tile, ofl_batch **out);
 void ofl_batch_destroy(ofl_batch *b);
 int ofl_batch_set_tile(ofl_batch *b, const ofl_tile *tile);
@@ -405,9 +411,10 @@ int ofl_batch_get_tile(const ofl_batch *b, ofl_tile *tile);
 
 /* Fusion for the batched iterations (OFL_FUSE_* as for ofl_set_fusion): the
  * batched sweep also emits each grid's residual partials, and/or the copy-back
- * becomes an exchange of every grid's p and wrk2 buffers (odd iterations read
- * a second view table with the two exchanged; after a run of odd length the
- * grids keep the exchange). EINVAL for unknown bits; ENOTSUP for
+ * becomes an exchange of every grid's p and wrk2 buffers (every second launch
+ * reads a second view table with the two exchanged; after an odd number of
+ * exchanges the grids keep it). Iterations that go two per launch do both
+ * anyway; the bits then say how the remaining single ones run. EINVAL for unknown bits; ENOTSUP for
  * OFL_FUSE_RESIDUAL on a batch of OFL_SUM_KAHAN_F32 grids (the fused residual
  * sums in FP64 only). */
 int ofl_batch_set_fusion(ofl_batch *b, unsigned flags);
