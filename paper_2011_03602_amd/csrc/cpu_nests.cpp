@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -48,10 +49,15 @@ void parallel_planes(int lo, int hi, long long work, F &&f) {
     for (int t = 0; t < nt; ++t) {
         const int a = lo + static_cast<int>(static_cast<long long>(n) * t / nt);
         const int b = lo + static_cast<int>(static_cast<long long>(n) * (t + 1) / nt);
-        pool.emplace_back([a, b, &f] {
+        auto part = [a, b, &f] {
             for (int k = a; k < b; ++k)
                 f(k);
-        });
+        };
+        try {
+            pool.emplace_back(part);
+        } catch (const std::system_error &) {  // no thread to be had
+            part();
+        }
     }
     for (auto &th : pool)
         th.join();
