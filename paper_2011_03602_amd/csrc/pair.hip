@@ -320,8 +320,8 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
     } else {
         j = j0 - 1 + wave;
         i0 = ts + lane * VEC;
-        pos = min(i0, ((I - 1) / VEC) * VEC);
-        cpos = min(pos, g.cpitch - VEC);
+        pos = pair_row_at(i0, I, VEC);
+        cpos = pair_coef_at(pos, g.cpitch, VEC);
         la = static_cast<long long>(min(max(j - 1, 0), g.J - 1)) * pitch;
         lc = static_cast<long long>(min(j, g.J - 1)) * pitch;
         lb = static_cast<long long>(min(j + 1, g.J - 1)) * pitch;
@@ -415,8 +415,8 @@ __device__ __forceinline__ void pair_march(const GridView &g, Shared<VEC, BF16, 
     unsigned db = cb;
     if constexpr (BF16) {
         const int at8 = (lane & 31) * 8;
-        db = 2u * static_cast<unsigned>(
-                      FLAT ? coef_at(min(max(ts + wave * S + at8, 0), pitch * g.J - 8), 8) : min(ts + at8, g.cpitch - 8));
+        db = 2u * static_cast<unsigned>(FLAT ? coef_at(min(max(ts + wave * S + at8, 0), pitch * g.J - 8), 8)
+                                             : pair_coef_at(ts + at8, g.cpitch, 8));
     }
     auto dma = [&](int t, int k, int slot, auto nt) {
         constexpr int kAux = decltype(nt)::value ? 2 : 0;
@@ -767,6 +767,8 @@ void by_format(const GridView &g, int bf16, const PairShape &s, float omega, dou
 
 void launch_pair(const GridView &g, int bf16, const PairShape &s, float omega, double *parts, const double *prev,
                  hipStream_t st) {
+    if (!s.flat && !pair_row_form(s.vec, bf16 ? 2 : 4, g.cpitch))
+        fail(OFL_EINVAL, "pair sweep: coefficient rows that 16-byte loads do not divide");
     if (s.flat && s.vec == 4 && s.waves == kPairBatchWaves && s.njt == 1) {
         if (bf16)
             pair_flat_kernel<true, kPairBatchWaves>

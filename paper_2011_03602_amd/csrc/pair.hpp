@@ -12,6 +12,25 @@ namespace ofl {
 // second step only: two, in whole lanes.
 __host__ __device__ inline constexpr int pair_margin(int vec) { return vec < 2 ? 2 : vec; }
 
+// Row form: where a lane whose points start at i0 loads its vec points of p, and
+// where it loads n coefficients for the points from i0. Loads that would pass the
+// row's end move back; no load that holds an interior point's value may move,
+// since its lane takes the values by position.
+__host__ __device__ inline constexpr int pair_row_at(int i0, int I, int vec) {
+    const int last = (I - 1) / vec * vec;
+    return i0 < last ? i0 : last;
+}
+__host__ __device__ inline constexpr int pair_coef_at(int i0, int cpitch, int n) {
+    return i0 < cpitch - n ? i0 : cpitch - n;
+}
+// bfloat16 coefficients at 4 points per lane travel in 16-byte loads of 8 points,
+// the last of which would move back by 4 in a row of 4 points more than a multiple
+// of 8 (and every other row would start 8 bytes off the load's size): such rows
+// take flat segments, whose loads run across row ends, or fewer points per lane.
+__host__ __device__ inline constexpr bool pair_row_form(int vec, int coef_elem, int cpitch) {
+    return vec < 4 || coef_elem == 4 || cpitch % 8 == 0;
+}
+
 // Decomposition of one grid's pair sweep: tiles of 64*vec points along i (which
 // overlap by two margins), waves-2 rows along j and `chunk` planes along k.
 struct PairShape {
@@ -65,6 +84,8 @@ inline bool pair_plan(int I, int J, int K, int pitch, int coef_elem, PairShape *
     for (const auto &form : kForms) {
         if (form.vec == 1 && I - 1 > kWave)
             continue;  // tiles of 60 points split cache lines
+        if (!pair_row_form(form.vec, coef_elem, pitch))
+            continue;  // by pitch: compact coefficient rows have p's, the default ones whole lines under a pitch of 32 k
         PairShape s;
         s.vec = form.vec;
         s.waves = form.waves;
