@@ -548,8 +548,9 @@ int ofl_grid_search_loops(ofl_grid *g, const ofl_ga_params *ga, int iters, float
  * ldc >= N (strides in elements). C must not overlap A or B. The library's
  * matrix-core kernels are queued (small and narrow products: FP32 instructions;
  * large ones: each value as the exact sum of three bfloat16 parts, six part
- * products, FP32 accumulation, with tiles whose values leave that form's range
- * computed in FP32; either way closer to the exact product than one FP32 sum
+ * products, FP32 accumulation, with 128 x 128 tiles that meet infinities, NaN,
+ * overflow, or values below 2^-103 beside values from 2^30 computed a second time
+ * in FP32, which takes over three times as long; either way closer to the exact product than one FP32 sum
  * over K, infinities and NaN as defined) on stream (a
  * hipStream_t; NULL: the default stream) and the call returns without
  * waiting. Nothing is read or written when M or N is 0; K = 0 sets C to 0.

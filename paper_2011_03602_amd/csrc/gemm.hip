@@ -228,10 +228,19 @@ __global__ __launch_bounds__(KS * 64) void gemm_direct_kernel(GemmArgs g, int ti
 // rate a library's large bfloat16 product reaches on this card (1.11), whose
 // clock falls below 2 GHz under it.
 //
-// Values outside the split's range: parts of |x| < 2^-50 could fall below the
-// smallest normal number, and x beyond bfloat16's largest, infinite or NaN gives
-// infinite or NaN parts. A tile that met the former, or whose sums came out
-// infinite or NaN, is computed again with the FP32 instructions.
+// Range. Operands are split times 2^23 each and the sums stored times 2^-46: then
+// every part of every FP32 value, the smallest subnormal one's 2^-149 among them,
+// is a normal bfloat16 number (beside a product with a subnormal operand the
+// instruction drops up to 7 bits more of a lower addend), and the sums lose nothing
+// below the normal range that the results would keep. That leaves no room for
+// |x| from 2^104 or |C| from 2^82, so a tile whose first stages hold a value from
+// 2^30 splits its operands as they are, and looks out for nonzero values below
+// 2^-103, whose parts would be subnormal. A tile that meets one, or whose sums come
+// out infinite or NaN, is computed again with the FP32 instructions, straight from
+// global memory (4096^3 with every tile so: 3.4 ms): infinite and NaN operands,
+// overflow, and operands that mix those magnitudes. With operands always split as
+// they are and tiles redone below 2^-50, 4096^3 with one operand around 1e-18 took
+// 3355 us, now 727; around 1 or 1e30 720-746 before and now.
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
@@ -245,7 +254,8 @@ constexpr int kSplitTile = 128, kSplitK = 32, kParts = 3;
 // both halves of eight rows. No access conflicts (with k groups 640 bytes apart
 // and columns in order, a stage's 48 accesses per wave took 330 cycles more).
 constexpr int kK8Stride = 512 + 32, kTileStride = 4 * kK8Stride;
-constexpr unsigned kTinyBits = (127u - 50u) << 24;  // 2^-50, shifted left by one (no sign)
+constexpr float kSplitScale = 0x1p23f, kSplitLarge = 0x1p30f;
+constexpr unsigned kSplitTiny = (127u - 103u) << 24;  // 2^-103, shifted left by one (no sign)
 
 __device__ __forceinline__ void split2(float x, float y, unsigned (&p)[kParts]) {
 #pragma unroll
@@ -271,7 +281,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int GROUPS>
 __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g, int tiles_n) {
     __shared__ __attribute__((aligned(16))) char lds[GROUPS][2][kParts * 4 * kTileStride];
-    __shared__ int redo;
+    __shared__ int redo, large;
     const int tid = threadIdx.x % 256, lane = tid & 63;
     const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -327,15 +337,17 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
                                ? g.B[static_cast<size_t>(k0 + bk + q) * g.ldb + min(bs + e, g.N - 1)]
                                : 0.f;
     };
+    float scale = kSplitScale;
     unsigned tiny = 0xffffffffu;  // smallest nonzero |x| seen, shifted left, less one (zero wraps to the top)
     auto stash = [&] {
+        if (scale == 1.f)
+#pragma unroll
+            for (int t = 0; t < 32; ++t)
+                tiny = min(tiny, (__float_as_uint(t < 16 ? ra[t / 4][t % 4] : rb[t / 4 - 4][t % 4]) << 1) - 1u);
         auto put = [&](char *base, int tile, int row, int k, const float *v) {
             unsigned lo[kParts], hi[kParts];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                tiny = min(tiny, (__float_as_uint(v[q]) << 1) - 1u);
-            split2(v[0], v[1], lo);
-            split2(v[2], v[3], hi);
+            split2(v[0] * scale, v[1] * scale, lo);
+            split2(v[2] * scale, v[3] * scale, hi);
 #pragma unroll
             for (int s = 0; s < kParts; ++s)
                 *reinterpret_cast<uintx2 *>(base + (s * 4 + tile) * kTileStride + k / 8 * kK8Stride + row * 16 +
@@ -395,11 +407,24 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
         }
     };
     if (threadIdx.x == 0)
-        redo = 0;
+        redo = large = 0;
     const int stages = (g.K + kSplitK - 1) / kSplitK;
+    lds_barrier();
+    if (group < stages) {
+        fetch(group * kSplitK);
+        float top = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                top = fmaxf(top, fmaxf(fabsf(ra[i][q]), fabsf(rb[i][q])));
+        if (top >= kSplitLarge)
+            large = 1;
+    }
+    lds_barrier();
+    if (__builtin_amdgcn_readfirstlane(large) != 0)
+        scale = 1.f;
     if constexpr (GROUPS == 1) {
-        if (stages > 0)
-            fetch(0);
         for (int p = 0; p < stages; ++p) {
             stash();
             lds_barrier();
@@ -411,8 +436,6 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
         }
     } else {
         // phase p: group p % 2 multiplies stage p while the other writes stage p + 1
-        if (group < stages)
-            fetch(group * kSplitK);
         if (group == 0 && stages > 0)
             stash();
         lds_barrier();
@@ -438,7 +461,7 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
             for (int r = 0; r < 16; ++r)
                 top = max(top, __float_as_uint(acc[i][j][r]) & 0x7fffffffu);
     __syncthreads();  // redo is cleared, and the stages are read
-    if (tiny < kTinyBits - 1u || top >= 0x7f800000u)
+    if (tiny < kSplitTiny - 1u || top >= 0x7f800000u)
         redo = 1;
     __syncthreads();
     if (redo != 0) {
@@ -461,12 +484,14 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
     constexpr int kHalf = kSplitTile / 2 * kSplitTile;
     float *out = reinterpret_cast<float *>(&lds[0][0][0]);
     static_assert(GROUPS * kHalf * sizeof(float) <= sizeof lds, "the sums fit the stages' place");
+    const float unscale = 1.f / (scale * scale);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             *reinterpret_cast<floatx2 *>(out + group * kHalf + (wm * 16 + Mfma<32>::row(lane, r)) * kSplitTile +
-                                         4 * (lane % 32) + wn) = floatx2{acc[i][0][r], acc[i][1][r]};
+                                         4 * (lane % 32) + wn) =
+                floatx2{acc[i][0][r] * unscale, acc[i][1][r] * unscale};
         __syncthreads();
         for (int e = threadIdx.x; e < kHalf / 4; e += 256 * GROUPS) {
             float4u v = *reinterpret_cast<const floatx4 *>(out + 4 * e);
