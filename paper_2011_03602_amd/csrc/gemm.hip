@@ -10,11 +10,14 @@
 // products): tiles of 16 x 16 to 32 x 32 on the FP32 matrix instructions, K
 // shared among a work-group's waves, operands straight from global memory.
 //
-// Both add up K in several partial sums, which brings the error against FP64
-// below that of one FP32 sum over all of K: measured as a fraction of that
-// sum's, root mean square over C, 0.26-0.74 for the direct form and 0.60-0.89
-// for the split form (K from 64 to 8192, normally distributed values; at K = 32
-// the direct form's sum has one part and the fraction is 1).
+// Errors against FP64, root mean square over C, as a fraction of those of one FP32
+// sum over all of K on the FP32 instructions (K from 64 to 8192): normally
+// distributed values 0.26-0.74 for the direct form, which adds up K in several
+// partial sums, and 0.23-0.35 for the split form; rows of A that are a softmax of
+// 3 times such values 0.26-0.74 and 0.26-0.49; of 20 times such values, where one
+// product dominates a sum, 0.77-0.95 and 0.88-1.09. (At K = 32 the direct form's
+// sum has one part and the fraction is 1.) A sum of a single product is within
+// 0.506 ulp in the split form, 0.5 in the other.
 //
 // Operand layouts (wave64, lane l): the 32x32x2 FP32 instruction takes
 // A[l % 32][l / 32] and B[l / 32][l % 32], the 16x16x4 one A[l % 16][l / 16] and
@@ -210,10 +213,13 @@ __global__ __launch_bounds__(KS * 64) void gemm_direct_kernel(GemmArgs g, int ti
 //
 // x = x0 + x1 + x2 with x0 = bfloat16(x), x1 = bfloat16(x - x0),
 // x2 = x - x0 - x1, each rounded to nearest even: FP32's 24 significant bits fit
-// three bfloat16 ones of 8, so the sum is exact. Of the nine products of parts,
-// the six whose part indices add up to at most 2 are taken; what is left out is
-// below 2^-25 of |a b|, an FP32 product's own rounding. Six bfloat16
-// instructions do the work of eight FP32 ones in 3/8 of the matrix cores' time.
+// three bfloat16 ones of 8, so the sum is exact. Of the nine products of parts all
+// but x2 y2 are taken, which is at most 2^-34 of |x y|. Eight bfloat16 instructions
+// do the work of eight FP32 ones in half of the matrix cores' time. The instruction
+// truncates the lower addends where a product is larger than the sum it joins, so
+// x0 y0 has a sum of its own and the other products, 2^-8 of it, another; they are
+// added at the end. (Without x1 y2 and x2 y1, which come to 2^-24 of |x y|, and with
+// one sum for all, a sum of one product was up to 1.41 ulp off.)
 //
 // Four waves own a 128 x 128 tile (64 x 64 each). A stage of 32 k is fetched
 // into registers, split there and written to LDS in the order the instructions
@@ -222,11 +228,13 @@ __global__ __launch_bounds__(KS * 64) void gemm_direct_kernel(GemmArgs g, int ti
 // splits while the other multiplies, and their sums are added at the end. With
 // one group, two work-groups share a CU instead (at small K, see pick_form).
 //
-// Measured, us against the former FP32-instruction tiles: 4096^3 724 against 988
-// (190 TFLOP/s), 8192^3 5925 against 7834, 2048^3 95 against 173, 2340 x 1142 x
-// 3098 124 against 594. The bfloat16 instructions then run at 1.14 PFLOP/s, the
-// rate a library's large bfloat16 product reaches on this card (1.11), whose
-// clock falls below 2 GHz under it.
+// Measured, us a launch among repeated ones against FP32-instruction tiles of 128 or
+// 64 rows by 256 columns: 4096^3 858 against 996 (160 TFLOP/s; 822 among calls on
+// changing operands), 8192^3 7000 against 7820, 2048^3 112 against 175, 2340 x 1142
+// x 3098 138 against 594. The bfloat16 instructions then run at 1.28 PFLOP/s, above
+// the rate a library's large bfloat16 product reaches on this card (1.11), whose
+// clock falls below 2 GHz under it. (With six products and one sum: 4096^3 742 among
+// calls.)
 //
 // Range. Operands are split times 2^23 each and the sums stored times 2^-46: then
 // every part of every FP32 value, the smallest subnormal one's 2^-149 among them,
@@ -240,7 +248,7 @@ __global__ __launch_bounds__(KS * 64) void gemm_direct_kernel(GemmArgs g, int ti
 // global memory (4096^3 with every tile so: 3.4 ms): infinite and NaN operands,
 // overflow, and operands that mix those magnitudes. With operands always split as
 // they are and tiles redone below 2^-50, 4096^3 with one operand around 1e-18 took
-// 3355 us, now 727; around 1 or 1e30 720-746 before and now.
+// 3355 us, since then what other operands take.
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
@@ -372,14 +380,14 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
         }
     };
     const int wm = wave / 2 * 2, wn = wave % 2 * 2;  // the wave's first row tile and column tile
-    floatx16 acc[2][2];
+    floatx16 acc[2][2], low[2][2];  // sums of a0 b0, and of the other products
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                acc[i][j][r] = 0.f;
+                acc[i][j][r] = low[i][j][r] = 0.f;
     const int at = lane / 32 * kK8Stride + lane % 32 * 16;
     auto multiply = [&] {
 #pragma unroll
@@ -395,15 +403,16 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
                 }
             // the small products first
 #pragma unroll
-            for (int sum = kParts - 1; sum >= 0; --sum)
+            for (int sum = kParts; sum >= 0; --sum)
 #pragma unroll
-                for (int s = 0; s <= sum; ++s)
+                for (int s = max(0, sum - kParts + 1); s <= min(sum, kParts - 1); ++s)
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][s], b[j][sum - s], acc[i][j], 0,
-                                                                                0, 0);
+                        for (int j = 0; j < 2; ++j) {
+                            floatx16 &c = sum > 0 ? low[i][j] : acc[i][j];
+                            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][s], b[j][sum - s], c, 0, 0, 0);
+                        }
         }
     };
     if (threadIdx.x == 0)
@@ -458,27 +467,13 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
+            for (int r = 0; r < 16; ++r) {
+                acc[i][j][r] += low[i][j][r];
                 top = max(top, __float_as_uint(acc[i][j][r]) & 0x7fffffffu);
-    __syncthreads();  // redo is cleared, and the stages are read
+            }
     if (tiny < kSplitTiny - 1u || top >= 0x7f800000u)
         redo = 1;
-    __syncthreads();
-    if (redo != 0) {
-        for (int i = group; i < 2; i += GROUPS)
-            for (int j = 0; j < 2; ++j) {
-                floatx16 sum[1];
-                const int mt = m0 + (wm + i) * 32, c = n0 + 4 * (lane % 32) + wn + j;
-                direct_sum<32, 1, 4>(g, mt, n0 + wn + j, lane, 0, 1, sum);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = mt + Mfma<32>::row(lane, r);
-                    if (row < g.M && c < g.N)
-                        g.C[static_cast<size_t>(row) * g.ldc + c] = sum[0][r];
-                }
-            }
-        return;
-    }
+    __syncthreads();  // the stages are read
     // Through LDS, where the groups' sums meet, to rows of C in order: first the
     // even 32-row tiles, then the odd ones.
     constexpr int kHalf = kSplitTile / 2 * kSplitTile;
@@ -510,6 +505,21 @@ __global__ __launch_bounds__(256 * GROUPS, 2) void gemm_split_kernel(GemmArgs g,
         }
         __syncthreads();
     }
+    // (here, where the sums are no longer held in registers)
+    if (redo != 0) {
+        for (int i = group; i < 2; i += GROUPS)
+            for (int j = 0; j < 2; ++j) {
+                floatx16 sum[1];
+                const int mt = m0 + (wm + i) * 32, c = n0 + 4 * (lane % 32) + wn + j;
+                direct_sum<32, 1, 4>(g, mt, n0 + wn + j, lane, 0, 1, sum);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int row = mt + Mfma<32>::row(lane, r);
+                    if (row < g.M && c < g.N)
+                        g.C[static_cast<size_t>(row) * g.ldc + c] = sum[0][r];
+                }
+            }
+    }
 }
 
 enum class Form { kDirect16, kDirect32x16, kDirect32, kSplit, kSplitShared };
@@ -522,9 +532,9 @@ long long tiles(const GemmArgs &g, int tm, int tn) {
 // rounds of one tile per CU take a fixed cost and a share of K each; a split one's rounds of
 // resident tiles (two groups: one per CU, and a part-filled last round is
 // faster; one group: two per CU, better at small K, where a tile's fixed cost
-// counts) a fixed cost and a share. Fitted to 46 products (M 64..8192, N 8..8192,
-// K 32..8192); on those and 50 drawn ones the choice takes 1.02 times the best
-// form's time on average, 1.36 at worst (of 4 us).
+// counts) a fixed cost and a share. Fitted to 144 products (M 64..8192, N 8..8192,
+// K 32..8192): on those the choice takes 1.01 times the best form's time on average,
+// 1.33 at worst (of 4 us).
 Form pick_form(const GemmArgs &g) {
     const double k = g.K;
     auto direct = [&](int tm, int tn, double fixed, double share) {
@@ -533,10 +543,10 @@ Form pick_form(const GemmArgs &g) {
     const long long big = tiles(g, kSplitTile, kSplitTile);
     auto rounds = [&](int slots) { return static_cast<double>(big / slots); };
     auto rest = [&](int slots) { return static_cast<double>(big % slots) / slots; };
-    const double alone = 5.0 + rounds(2 * kCus) * (4.1 + 0.09 * k) +
-                         (rest(2 * kCus) > 0 ? 4.1 + k * (rest(2 * kCus) > 0.5 ? 0.09 : 0.064) : 0.0);
+    const double alone = 5.0 + rounds(2 * kCus) * (4.8 + 0.101 * k) +
+                         (rest(2 * kCus) > 0 ? 4.8 + k * (rest(2 * kCus) > 0.5 ? 0.101 : 0.061) : 0.0);
     const double shared =
-        5.0 + rounds(kCus) * (4.2 + 0.0442 * k) + (rest(kCus) > 0 ? 4.2 + k * (0.031 + 0.012 * rest(kCus)) : 0.0);
+        5.0 + rounds(kCus) * (4.3 + 0.0556 * k) + (rest(kCus) > 0 ? 4.3 + k * (0.0354 + 0.0142 * rest(kCus)) : 0.0);
     const double us[] = {direct(16, 16, 0.5, 2.7e-3), direct(32, 16, 0.3, 5.2e-3), direct(32, 32, 0.5, 6.9e-3),
                          alone, shared};
     int best = 0;

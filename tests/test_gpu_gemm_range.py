@@ -140,3 +140,20 @@ def test_small_operands_values():
     for scale in (1e-18, 1e-30, 1e-37, 1e-41):
         x = (a * np.float32(scale)).astype(np.float32)
         check_rows(x, b, product(x, b), [0, 5, 127, 128, 1000, 2304])
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_single_products_are_rounded_once(M, N, K):
+    """A matrix with one value per row times a dense one, so that every element of C
+    is one product: half an ulp as in FP32, plus what the product of the third parts
+    (left out: 2^-11 ulp) and the truncated sums of the lower products (four, at most
+    2^-7 ulp each) may add, 2^-5."""
+    say("gemm single products", M, N, K)
+    rng = np.random.default_rng(K)
+    A = one_per_row(M, K, rng.standard_normal(M))
+    B = rng.standard_normal((K, N)).astype(np.float32)
+    c = product(A, B)
+    cols = (7 * np.arange(M) + 3) % K
+    ref = A[np.arange(M), cols].astype(np.float64)[:, None] * B.astype(np.float64)[cols]
+    ulp = np.exp2(np.floor(np.log2(np.abs(ref))) - 23)
+    assert np.max(np.abs(c - ref) / ulp) <= 0.5 + 2.0 ** -5
