@@ -549,9 +549,14 @@ Form pick_form(const GemmArgs &g) {
         5.0 + rounds(kCus) * (4.3 + 0.0556 * k) + (rest(kCus) > 0 ? 4.3 + k * (0.0354 + 0.0142 * rest(kCus)) : 0.0);
     const double us[] = {direct(16, 16, 0.5, 2.7e-3), direct(32, 16, 0.3, 5.2e-3), direct(32, 32, 0.5, 6.9e-3),
                          alone, shared};
-    int best = 0;
-    for (int f = 1; f < 5; ++f)
-        if (us[f] < us[best])
+    // A launch holds fewer than 2^32 threads; past that the count wraps without an
+    // error and most of C is not written. Few rows of 2^28 columns would be past it in
+    // 16- or 32-column tiles; kSplit, with two threads per column, always fits.
+    const long long threads[] = {1024 * tiles(g, 16, 16), 512 * tiles(g, 32, 16), 512 * tiles(g, 32, 32), 256 * big,
+                                 512 * big};
+    int best = static_cast<int>(Form::kSplit);
+    for (int f = 0; f < 5; ++f)
+        if (us[f] < us[best] && threads[f] < (1LL << 32))
             best = f;
     return static_cast<Form>(best);
 }

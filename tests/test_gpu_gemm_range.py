@@ -157,3 +157,21 @@ def test_single_products_are_rounded_once(M, N, K):
     ref = A[np.arange(M), cols].astype(np.float64)[:, None] * B.astype(np.float64)[cols]
     ulp = np.exp2(np.floor(np.log2(np.abs(ref))) - 23)
     assert np.max(np.abs(c - ref) / ulp) <= 0.5 + 2.0 ** -5
+
+
+@pytest.mark.parametrize("M,K", [(1, 1), (2, 3)])
+def test_rows_of_more_columns_than_small_tiles_reach(M, K):
+    """2^28 columns and more: launches of small tiles would hold 2^32 threads."""
+    N = (1 << 28) + 40
+    say("gemm long rows", M, N, K)
+    a = torch.randn((M, K), device="cuda")
+    b = torch.randn((K, N), device="cuda")
+    c = torch.full((M, N), 7.0, device="cuda")
+    ofl.ofl_gemm_f32(M, N, K, a.data_ptr(), K, b.data_ptr(), N, c.data_ptr(), N, None)
+    torch.cuda.synchronize()
+    for first in range(0, N, 1 << 25):
+        part = slice(first, min(first + (1 << 25), N))
+        x = b[:, part].double()
+        ref = sum(a[:, k:k + 1].double() * x[k:k + 1] for k in range(K))
+        mag = sum(a[:, k:k + 1].double().abs() * x[k:k + 1].abs() for k in range(K))
+        assert bool(((c[:, part].double() - ref).abs() <= 2.0 * K * 2.0 ** -24 * mag).all())
