@@ -60,6 +60,16 @@ void free_tables(ofl_batch *b) {
     b->tables_ready = false;
 }
 
+}  // namespace
+
+void batch_drop_tables(ofl_batch *b) {
+    hip_check(hipSetDevice(b->device), "hipSetDevice");
+    hip_check(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
+    free_tables(b);
+}
+
+namespace {
+
 template <class T>
 void upload(void *&dst, const std::vector<T> &src, hipStream_t s) {
     free_dev(dst);
@@ -681,11 +691,10 @@ int ofl_batch_set_tile(ofl_batch *b, const ofl_tile *tile) {
         if (tile->vec == 8)
             fail(OFL_ENOTSUP, "batched sweeps run 1, 2 or 4 points per lane (tile.vec 8 is for single grids)");
         const TileCfg c = to_cfg(*tile);
-        if (c.vec != b->tile.vec || c.rows != b->tile.rows || c.kchunk != b->tile.kchunk ||
+        // the tables of a batch without a tile of its own hold a list of pairs
+        if (!b->tile_chosen || c.vec != b->tile.vec || c.rows != b->tile.rows || c.kchunk != b->tile.kchunk ||
             c.flags != b->tile.flags || c.occupancy != b->tile.occupancy) {
-            hip_check(hipSetDevice(b->device), "hipSetDevice");
-            hip_check(hipStreamSynchronize(b->stream), "hipStreamSynchronize");
-            free_tables(b);
+            batch_drop_tables(b);
             b->tile = c;
         }
         b->tile_chosen = true;

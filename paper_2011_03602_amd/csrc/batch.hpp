@@ -58,6 +58,7 @@ struct ofl_batch {
 namespace ofl {
 
 void batch_build_tables(ofl_batch *b);
+void batch_drop_tables(ofl_batch *b);
 void batch_prepare(ofl_batch *b);
 void batch_enqueue(ofl_batch *b, int iters, float omega);
 void batch_launch(ofl_batch *b, int iters, float omega);

@@ -1,0 +1,102 @@
+/* When iterations go in pairs, on the stand-in HIP runtime (hip_stand_in.cpp) with
+ * launchers that count (pair_count.cpp): whatever was called before, a tile of the
+ * caller's turns pairs off. */
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include "ofl.h"
+
+long pair_launches(void);
+long pair_batch_launches(void);
+long stand_in_alloc_calls(void);
+
+#define CHECK(c)                                                                                       \
+    do {                                                                                               \
+        if (!(c)) {                                                                                    \
+            fprintf(stderr, "FAIL %s:%d: %s (last error: %s)\n", __FILE__, __LINE__, #c,               \
+                    ofl_last_error());                                                                 \
+            return 1;                                                                                  \
+        }                                                                                              \
+    } while (0)
+
+typedef struct {
+    float *arr[14];
+    ofl_grid *g;
+} problem;
+
+static int make(problem *pb, int I, int J, int K) {
+    const size_t n = (size_t)I * J * K;
+    ofl_grid_desc d;
+    memset(&d, 0, sizeof d);
+    for (int a = 0; a < 14; ++a) {
+        pb->arr[a] = (float *)malloc(n * sizeof(float));
+        for (size_t t = 0; t < n; ++t)
+            pb->arr[a][t] = a == 3 ? 1.0f / 6.0f : (a < 3 || (a >= 7 && a <= 10) ? 1.0f : 0.25f);
+        if (a < 12)
+            d.coef[a] = pb->arr[a];
+    }
+    d.I = I;
+    d.J = J;
+    d.K = K;
+    d.p = pb->arr[12];
+    d.wrk2 = pb->arr[13];
+    d.device = -1;
+    return ofl_grid_create(&d, &pb->g);
+}
+
+static void drop(problem *pb) {
+    ofl_grid_destroy(pb->g);
+    for (int a = 0; a < 14; ++a)
+        free(pb->arr[a]);
+}
+
+/* Pair launches of one run, which captures its graph again when something changed. */
+static long grid_pairs(ofl_grid *g, int iters) {
+    const long n = pair_launches();
+    double x;
+    return ofl_jacobi_run(g, iters, 0.8f, &x) == OFL_OK ? pair_launches() - n : -1;
+}
+
+static long batch_pairs(ofl_batch *b, int iters) {
+    const long n = pair_batch_launches();
+    double x[2];
+    return ofl_batch_run(b, iters, 0.8f, x) == OFL_OK ? pair_batch_launches() - n : -1;
+}
+
+static int batch_tiles(void) {
+    problem pb[2];
+    CHECK(make(&pb[0], 37, 19, 17) == OFL_OK && make(&pb[1], 41, 23, 20) == OFL_OK);
+    ofl_grid *grids[2] = {pb[0].g, pb[1].g};
+    ofl_tile t;
+    for (int run_first = 0; run_first < 2; ++run_first) {
+        ofl_batch *b = NULL;
+        CHECK(ofl_batch_create(grids, 2, NULL, &b) == OFL_OK);
+        if (run_first)
+            CHECK(batch_pairs(b, 7) == 3);
+        CHECK(ofl_batch_get_tile(b, &t) == OFL_OK && ofl_batch_set_tile(b, &t) == OFL_OK);
+        CHECK(batch_pairs(b, 7) == 0 && batch_pairs(b, 9) == 0);
+        ofl_batch_destroy(b);
+    }
+    drop(&pb[0]);
+    drop(&pb[1]);
+    return 0;
+}
+
+static int grid_tiles(void) {
+    problem pb;
+    ofl_tile t;
+    CHECK(make(&pb, 37, 19, 17) == OFL_OK);
+    CHECK(grid_pairs(pb.g, 7) == 3);
+    CHECK(ofl_get_tile(pb.g, &t) == OFL_OK && ofl_set_tile(pb.g, &t) == OFL_OK);
+    CHECK(grid_pairs(pb.g, 7) == 0);
+    drop(&pb);
+    return 0;
+}
+
+int main(void) {
+    if (batch_tiles() || grid_tiles())
+        return 1;
+    printf("pair policy ok\n");
+    return 0;
+}
