@@ -888,8 +888,10 @@ int ofl_batch_tune(ofl_batch *b, const ofl_ga_params *ga_in, ofl_tune_result *ou
             grid_sync(g);
             saved.emplace_back(g->p, g->p + g->n);
         }
-        batch_prepare(b);
         const TileCfg old = b->tile;
+        const bool chosen = b->tile_chosen;
+        batch_drop_tables(b);
+        b->tile_chosen = true;  // the runs measure the tile, the one they start from too: no iterations in pairs
         std::map<uint32_t, bool> checked;
         auto evaluate = [&](uint32_t gene) -> double {
             TileCfg t;
@@ -906,8 +908,16 @@ int ofl_batch_tune(ofl_batch *b, const ofl_ga_params *ga_in, ofl_tune_result *ou
             return ms;
         };
         ofl_tune_result res{};
-        TuneCache cache(cache_path(), batch_key(b, ga));
-        run_ga(ga, true, encode(old, true), cache, evaluate, &res);
+        try {
+            batch_prepare(b);
+            TuneCache cache(cache_path(), batch_key(b, ga));
+            run_ga(ga, true, encode(old, true), cache, evaluate, &res);
+        } catch (...) {
+            b->tile = old;
+            b->tile_chosen = chosen;
+            batch_drop_tables(b);
+            throw;
+        }
         const ofl_tile best = res.best;
         if (ofl_batch_set_tile(b, &best) != OFL_OK)
             fail(OFL_EINVAL, ofl_last_error());
