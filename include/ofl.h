@@ -190,8 +190,8 @@ int ofl_get_regions(const ofl_grid *g, unsigned *mask, int level[3], int *xfer_m
  * until ofl_update_host/ofl_data_exit. *gosa_out (nullable) receives R of the
  * last iteration, i.e. the residual of the iterate before the last update;
  * iters == 0 leaves p alone and gives NaN. With every nest on the GPU as one
- * region, hoisted transfers, no tile set or searched, profiling off and outside
- * a batch, the iterations before the last run two per launch (one pass over the
+ * region, hoisted transfers, no tile set (nor searched and faster without),
+ * profiling off and outside a batch, the iterations before the last run two per launch (one pass over the
  * read-only arrays serves both; p is bitwise the same, and so is gosa, which the
  * last iteration computes by itself; wrk2's device content after such a run is
  * unspecified, as after a fused one). EINVAL for iters < 0 or omega == 0 or
@@ -399,10 +399,11 @@ typedef struct ofl_batch ofl_batch;
  * XCD receives runs of consecutive lines (which share halo rows). A grid created
  * with a compact desc.row_align whose rows fill few of a wave's lanes runs in
  * packed rows: each wave covers 64 * vec consecutive points of a plane across
- * row ends. While no tile is set or searched, the iterations before a run's
+ * row ends. While no tile is set, the iterations before a run's
  * last go two per launch for all grids (as in ofl_jacobi_run), each work-group
  * covering consecutive points of a plane across row ends; the tile is that of
- * the remaining single iterations. EINVAL for n < 1, NULL grids, mixed devices
+ * the remaining single iterations. (A searched tile leaves that on unless single
+ * iterations with it are faster, see ofl_batch_tune.) EINVAL for n < 1, NULL grids, mixed devices
  * or formats. */
 int ofl_batch_create(ofl_grid *const *grids, int n, const ofl_tile *tile, ofl_batch **out);
 void ofl_batch_destroy(ofl_batch *b);
@@ -453,7 +454,11 @@ typedef struct ofl_tune_result {
  * nests beyond the tolerance gets infinite time (Sec. 4.2.2), the rest are
  * timed with HIP events; roulette selection on 1/sqrt(time), single-point
  * crossover, per-bit mutation and elite copy make the next generation. The
- * best tile is also applied to the grid/batch. p is restored on return. */
+ * best tile is also applied to the grid/batch. p is restored on return. Genes are
+ * timed in single iterations, as runs with that tile set by ofl_set_tile or
+ * ofl_batch_set_tile go, and best_ms is such a time; afterwards the best tile is
+ * timed once more, over at least 3 iterations, with two iterations per launch where
+ * the run allows that, and the faster way stays in place (until a tile is set). */
 int ofl_grid_tune(ofl_grid *g, const ofl_ga_params *ga, ofl_tune_result *out);
 int ofl_batch_tune(ofl_batch *b, const ofl_ga_params *ga, ofl_tune_result *out);
 

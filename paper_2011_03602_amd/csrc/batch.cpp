@@ -240,7 +240,7 @@ std::vector<PairItem> pair_items(const ofl_batch *b, std::vector<int> *range) {
     const int n = static_cast<int>(b->grids.size());
     std::vector<PairItem> items;
     range->assign(static_cast<size_t>(n) + 1, 0);
-    if (b->tile_chosen || launch_pair_batch == nullptr)
+    if (b->single_only || launch_pair_batch == nullptr)
         return items;
     std::vector<int> segs(static_cast<size_t>(n));
     double points = 0.0;
@@ -652,7 +652,7 @@ int ofl_batch_create(ofl_grid *const *grids, int n, const ofl_tile *tile, ofl_ba
         b->sum_mode = grids[0]->sum_mode;
         if (tile) {
             b->tile = to_cfg(*tile);
-            b->tile_chosen = true;
+            b->tile_chosen = b->single_only = true;
         } else {
             b->tile = batch_default_tile(b->fmt, 0);
         }
@@ -691,13 +691,13 @@ int ofl_batch_set_tile(ofl_batch *b, const ofl_tile *tile) {
         if (tile->vec == 8)
             fail(OFL_ENOTSUP, "batched sweeps run 1, 2 or 4 points per lane (tile.vec 8 is for single grids)");
         const TileCfg c = to_cfg(*tile);
-        // the tables of a batch without a tile of its own hold a list of pairs
-        if (!b->tile_chosen || c.vec != b->tile.vec || c.rows != b->tile.rows || c.kchunk != b->tile.kchunk ||
+        // the tables hold a list of pairs unless single_only was set
+        if (!b->single_only || c.vec != b->tile.vec || c.rows != b->tile.rows || c.kchunk != b->tile.kchunk ||
             c.flags != b->tile.flags || c.occupancy != b->tile.occupancy) {
             batch_drop_tables(b);
             b->tile = c;
         }
-        b->tile_chosen = true;
+        b->tile_chosen = b->single_only = true;
     });
 }
 

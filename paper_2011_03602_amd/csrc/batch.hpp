@@ -15,6 +15,7 @@ struct ofl_batch {
     hipStream_t stream = nullptr;
     ofl::TileCfg tile;
     bool tile_chosen = false;  // set by the caller or a search: fusion leaves it as it is
+    bool single_only = false;  // no iterations in pairs: the caller's tile, or a searched one that beats them
 
     unsigned fusion = 0;  // OFL_FUSE_* bits for the batched iterations
 

@@ -664,12 +664,14 @@ bool same_tile(const TileCfg &a, const TileCfg &b) {
 // last iteration of a run always goes nest by nest (or as the fused sweep), so
 // gosa is summed as ever, and an odd one runs first.
 //
-// A tile the caller chose or searched, profiling and a time limit (which look
-// at single nests) and grids inside a batch (whose tables hold the buffers)
-// keep single iterations.
-bool pair_eligible(ofl_grid *g, int iters) {
+// A tile the caller chose (or a searched one that is faster so), profiling and a
+// time limit (which look at single nests) and grids inside a batch (whose tables
+// hold the buffers) keep single iterations.
+}  // namespace
+
+bool grid_pair_eligible(ofl_grid *g, int iters) {
     if (launch_pair == nullptr || iters < 3 || g->mask != OFL_MASK_ALL_GPU || g->mode != OFL_XFER_HOISTED ||
-        g->profiling || g->deadline_ns != 0 || g->batch_refs != 0 || g->tile_chosen || !grid_whole_nests(g))
+        g->profiling || g->deadline_ns != 0 || g->batch_refs != 0 || g->single_only || !grid_whole_nests(g))
         return false;
     if (!g->pair_planned) {
         const int pitch = round_up(g->I, g->row_align > 0 ? g->row_align : kPitchAlign);
@@ -679,6 +681,8 @@ bool pair_eligible(ofl_grid *g, int iters) {
     }
     return g->pair.vec != 0;
 }
+
+namespace {
 
 // Pairs and their last sums on the grid's stream. The partials (two buffers of
 // two sums per work-group) live in the transfer staging buffer, which is idle
@@ -844,7 +848,7 @@ void run_pairs(ofl_grid *g, int from, int pairs, float omega) {
 // iterations ran (0: none of it applies).
 template <class Single>
 int run_in_pairs(ofl_grid *g, int iters, float omega, Single &&single) {
-    if (!pair_eligible(g, iters))
+    if (!grid_pair_eligible(g, iters))
         return 0;
     const int odd = (iters - 1) & 1;
     if (odd)
@@ -955,13 +959,13 @@ namespace {
 
 // The residual as one kernel for sweep and terms and one for their sum and its
 // way to the host, where sums are FP64, the nests whole on the GPU with hoisted
-// transfers and no tile was chosen. Sweep, residual, finalize and a copy took
+// transfers and no tile keeps single iterations. Sweep, residual, finalize and a copy took
 // 39 us at 65x65x129 (18 of them kernels), this 22 (12). The partial sums use the
 // transfer staging buffer, idle between transfers and ordered with them by the
 // stream.
 bool residual_in_one_sweep(ofl_grid *g, double *gosa) {
     if (launch_fold_publish == nullptr || (g->mask & 3u) != 3u || g->mode != OFL_XFER_HOISTED ||
-        g->level[kS] != OFL_LEVEL_K || g->level[kR] != OFL_LEVEL_K || g->sum_mode != OFL_SUM_F64 || g->tile_chosen ||
+        g->level[kS] != OFL_LEVEL_K || g->level[kR] != OFL_LEVEL_K || g->sum_mode != OFL_SUM_F64 || g->single_only ||
         g->deadline_ns != 0)
         return false;
     const TileCfg tile = default_tile(g->I, g->fmt, OFL_FUSE_RESIDUAL);
@@ -1438,7 +1442,7 @@ int ofl_set_tile(ofl_grid *g, const ofl_tile *tile) {
         if (tile->vec == 8 && make_layout(g->I, g->J, g->K, g->fmt, g->row_align).pitch % 8 != 0)
             fail(OFL_EINVAL, "tile.vec 8 needs a row pitch that is a multiple of 8 elements (row_align 0, 8, 16 or 32)");
         g->tile = to_cfg(*tile);
-        g->tile_chosen = true;
+        g->tile_chosen = g->single_only = true;
     });
 }
 

@@ -32,6 +32,7 @@ struct ofl_grid {
     int level[3] = {OFL_LEVEL_K, OFL_LEVEL_K, OFL_LEVEL_K};  // where each GPU nest's region opens
     ofl::TileCfg tile;
     bool tile_chosen = false;  // set by ofl_set_tile or the tuner; else the default follows the fusion
+    bool single_only = false;  // no iterations in pairs: a tile of ofl_set_tile, or a searched one that beats them
     bool in_region = false;
     ofl::Validity valid = ofl::fresh_validity();
 
@@ -111,6 +112,8 @@ void grid_ensure_device(ofl_grid *g);
 void grid_sync(ofl_grid *g);
 void grid_exec(ofl_grid *g, const std::vector<Xfer> &xs);
 void *grid_array_ptr(ofl_grid *g, int a);
+// Whether a run of iters iterations goes in pairs (pair.hip).
+bool grid_pair_eligible(ofl_grid *g, int iters);
 void grid_run_loop(ofl_grid *g, int iters, float omega, int nests);
 double grid_fetch_gosa(ofl_grid *g);
 void grid_swap_p_wrk2(ofl_grid *g);

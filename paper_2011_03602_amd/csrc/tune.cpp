@@ -296,6 +296,35 @@ double time_batch(ofl_batch *b, const TileCfg &t, const ofl_ga_params &ga) {
     return median(ts);
 }
 
+// Whether a run whose iterations go in pairs where it has them is as fast as one
+// that runs them all one by one with the tile found; over at least 3 iterations,
+// the fewest that have a pair. Pairs take half the time or less of the best tile's
+// single iterations nearly everywhere, and a search has to leave them on there.
+bool pairs_beat(ofl_grid *g, const TileCfg &t, ofl_ga_params ga) {
+    ga.probe_iters = std::max(ga.probe_iters, 3);
+    struct Restore {  // profiling runs nest by nest, which is not what later runs do
+        ofl_grid *g;
+        bool profiling;
+        ~Restore() { g->profiling = profiling; }
+    } restore{g, g->profiling};
+    g->profiling = false;
+    g->single_only = false;
+    if (!grid_pair_eligible(g, ga.probe_iters))
+        return false;
+    const double pairs = time_grid(g, t, ga);
+    g->single_only = true;
+    return pairs <= time_grid(g, t, ga);
+}
+
+bool pairs_beat(ofl_batch *b, ofl_ga_params ga) {
+    ga.probe_iters = std::max(ga.probe_iters, 3);
+    const double single = time_batch(b, b->tile, ga);
+    b->single_only = false;
+    batch_drop_tables(b);
+    batch_build_tables(b);
+    return b->p_cnt > 0 && time_batch(b, b->tile, ga) <= single;
+}
+
 void check_params(const ofl_ga_params &ga) {
     if (ga.population < 2 || ga.generations < 1 || ga.elite < 0 || ga.elite > ga.population || ga.probe_iters < 1 ||
         ga.repeats < 1 || !(ga.crossover >= 0 && ga.crossover <= 1) || !(ga.mutation >= 0 && ga.mutation <= 1) ||
@@ -832,10 +861,10 @@ int ofl_grid_tune(ofl_grid *g, const ofl_ga_params *ga_in, ofl_tune_result *out)
         const unsigned mask = g->mask;
         const int mode = g->mode;
         const TileCfg old = g->tile;
-        const bool chosen = g->tile_chosen;
+        const bool chosen = g->tile_chosen, single = g->single_only;
         g->mask = OFL_MASK_ALL_GPU;
         g->mode = OFL_XFER_HOISTED;
-        g->tile_chosen = true;  // the runs measure the tile: no iterations in pairs
+        g->tile_chosen = g->single_only = true;  // the runs measure the tile: no iterations in pairs
         std::map<uint32_t, bool> checked;
         auto evaluate = [&](uint32_t gene) -> double {
             TileCfg t;
@@ -854,11 +883,13 @@ int ofl_grid_tune(ofl_grid *g, const ofl_ga_params *ga_in, ofl_tune_result *out)
         try {
             TuneCache cache(cache_path(), grid_key(g, ga));
             run_ga(ga, false, encode(old, false), cache, evaluate, &res);
+            g->single_only = !pairs_beat(g, to_cfg(res.best), ga);
         } catch (...) {
             g->mask = mask;
             g->mode = mode;
             g->tile = old;
             g->tile_chosen = chosen;
+            g->single_only = single;
             throw;
         }
         grid_sync(g);
@@ -889,9 +920,9 @@ int ofl_batch_tune(ofl_batch *b, const ofl_ga_params *ga_in, ofl_tune_result *ou
             saved.emplace_back(g->p, g->p + g->n);
         }
         const TileCfg old = b->tile;
-        const bool chosen = b->tile_chosen;
+        const bool chosen = b->tile_chosen, one_by_one = b->single_only;
         batch_drop_tables(b);
-        b->tile_chosen = true;  // the runs measure the tile, the one they start from too: no iterations in pairs
+        b->tile_chosen = b->single_only = true;  // the runs measure the tile, the one they start from too: no iterations in pairs
         std::map<uint32_t, bool> checked;
         auto evaluate = [&](uint32_t gene) -> double {
             TileCfg t;
@@ -912,15 +943,21 @@ int ofl_batch_tune(ofl_batch *b, const ofl_ga_params *ga_in, ofl_tune_result *ou
             batch_prepare(b);
             TuneCache cache(cache_path(), batch_key(b, ga));
             run_ga(ga, true, encode(old, true), cache, evaluate, &res);
+            const ofl_tile best = res.best;
+            if (ofl_batch_set_tile(b, &best) != OFL_OK)
+                fail(OFL_EINVAL, ofl_last_error());
+            if (!pairs_beat(b, ga)) {
+                b->single_only = true;
+                batch_drop_tables(b);
+            }
+            batch_mark_done(b, 0);
         } catch (...) {
             b->tile = old;
             b->tile_chosen = chosen;
+            b->single_only = one_by_one;
             batch_drop_tables(b);
             throw;
         }
-        const ofl_tile best = res.best;
-        if (ofl_batch_set_tile(b, &best) != OFL_OK)
-            fail(OFL_EINVAL, ofl_last_error());
         for (size_t t = 0; t < b->grids.size(); ++t) {
             ofl_grid *g = b->grids[t];
             std::memcpy(g->p, saved[t].data(), saved[t].size() * sizeof(float));

@@ -1,6 +1,7 @@
 /* When iterations go in pairs, on the stand-in HIP runtime (hip_stand_in.cpp) with
  * launchers that count (pair_count.cpp): whatever was called before, a tile of the
- * caller's turns pairs off. */
+ * caller's turns pairs off. A search measures tiles without them and leaves them on
+ * unless it finds single iterations faster (the stand-in's times are all the same). */
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -94,8 +95,50 @@ static int grid_tiles(void) {
     return 0;
 }
 
+/* Nothing runs on the stand-in, so results are wrong: a tolerance that lets them pass. */
+static const ofl_ga_params kGa = {2, 1, 7, 0.9, 0.05, 1, 5, 1, 1e30};
+
+static int tuned(void) {
+    problem pb[2];
+    ofl_tune_result r;
+    ofl_tile t;
+    CHECK(make(&pb[0], 37, 19, 17) == OFL_OK && make(&pb[1], 41, 23, 20) == OFL_OK);
+    for (int profiling = 0; profiling < 2; ++profiling) {
+        CHECK(ofl_set_profiling(pb[0].g, profiling) == OFL_OK);
+        long n = pair_launches();
+        CHECK(ofl_grid_tune(pb[0].g, &kGa, &r) == OFL_OK);
+        CHECK(pair_launches() - n <= 2);  /* the comparison's graph of two pairs and nothing else */
+        CHECK(ofl_set_profiling(pb[0].g, 0) == OFL_OK);
+        CHECK(ofl_get_tile(pb[0].g, &t) == OFL_OK && memcmp(&t, &r.best, sizeof t) == 0);
+        CHECK(grid_pairs(pb[0].g, 7) == 3);
+        CHECK(ofl_set_tile(pb[0].g, &t) == OFL_OK && grid_pairs(pb[0].g, 7) == 0);
+    }
+    ofl_grid *grids[2] = {pb[0].g, pb[1].g};
+    ofl_batch *b = NULL;
+    CHECK(ofl_batch_create(grids, 2, NULL, &b) == OFL_OK);
+    for (int set_first = 0; set_first < 2; ++set_first) {
+        if (set_first)
+            CHECK(ofl_batch_get_tile(b, &t) == OFL_OK && ofl_batch_set_tile(b, &t) == OFL_OK);
+        long n = pair_batch_launches();
+        CHECK(ofl_batch_tune(b, &kGa, &r) == OFL_OK);
+        CHECK(pair_batch_launches() - n == 2);  /* the same */
+        CHECK(ofl_batch_get_tile(b, &t) == OFL_OK && memcmp(&t, &r.best, sizeof t) == 0);
+        CHECK(batch_pairs(b, 7) == 3);
+    }
+    /* a search that fails (nothing matches) leaves the batch as it was */
+    ofl_ga_params strict = kGa;
+    strict.tolerance = 1e-9;
+    CHECK(ofl_batch_set_tile(b, &t) == OFL_OK);
+    CHECK(ofl_batch_tune(b, &strict, &r) == OFL_ESTATE && batch_pairs(b, 7) == 0);
+    ofl_batch_destroy(b);
+    CHECK(ofl_grid_tune(pb[1].g, &strict, &r) == OFL_ESTATE && grid_pairs(pb[1].g, 7) == 3);
+    drop(&pb[0]);
+    drop(&pb[1]);
+    return 0;
+}
+
 int main(void) {
-    if (batch_tiles() || grid_tiles())
+    if (batch_tiles() || grid_tiles() || tuned())
         return 1;
     printf("pair policy ok\n");
     return 0;

@@ -1,4 +1,5 @@
-"""Tile searches measure the tiles they name in the iterations that such a tile runs."""
+"""Tile searches measure the tiles they name in the iterations that such a tile runs,
+and a tuned grid or batch is not slower than an untuned one."""
 
 import sys
 import time
@@ -93,3 +94,38 @@ def test_grid_search_times_its_first_tile_as_that_tile_runs(cache):
     ofl.ofl_data_exit(g.handle)
     g.close()
     assert measured > 0.7 * single
+
+
+def test_tuned_grid_is_not_slower():
+    """And it gives the same iterate. (The limit is the timing's noise; single
+    iterations take over twice the time of pairs here.)"""
+    say("grid tune, then run")
+    a = synth.make_problem(97, 61, 67, seed=51)
+    g, h = ofl.Grid(a), ofl.Grid(a)
+    for x in (g, h):
+        ofl.ofl_data_enter(x.handle)
+    r = ofl.ofl_grid_tune(h.handle, ofl.ga_params(population=4, generations=2, probe_iters=2, repeats=3))
+    assert ofl.ofl_get_tile(h.handle).as_dict() == r.best.as_dict()
+    x = ofl.ofl_jacobi_run(g.handle, 7, OMEGA)
+    y = ofl.ofl_jacobi_run(h.handle, 7, OMEGA)
+    ofl.ofl_update_host(g.handle)
+    ofl.ofl_update_host(h.handle)
+    assert np.array_equal(g.p, h.p) and abs(x - y) <= 1e-9 * abs(x)
+    plain = best_ms(lambda: ofl.ofl_jacobi_run(g.handle, PROBE, OMEGA))
+    tuned = best_ms(lambda: ofl.ofl_jacobi_run(h.handle, PROBE, OMEGA))
+    for x in (g, h):
+        ofl.ofl_data_exit(x.handle)
+        x.close()
+    assert tuned <= 1.25 * plain
+
+
+def test_tuned_batch_is_not_slower():
+    say("batch tune, then run")
+    b, grids = make_batch()
+    n = len(grids)
+    plain = best_ms(lambda: ofl.ofl_batch_run(b, PROBE, OMEGA, n))
+    r = ofl.ofl_batch_tune(b, ofl.ga_params(population=4, generations=2, probe_iters=10, repeats=3))
+    assert ofl.ofl_batch_get_tile(b).as_dict() == r.best.as_dict()
+    tuned = best_ms(lambda: ofl.ofl_batch_run(b, PROBE, OMEGA, n))
+    close(b, grids)
+    assert tuned <= 1.25 * plain
