@@ -664,14 +664,15 @@ bool same_tile(const TileCfg &a, const TileCfg &b) {
 // last iteration of a run always goes nest by nest (or as the fused sweep), so
 // gosa is summed as ever, and an odd one runs first.
 //
-// A tile the caller chose (or a searched one that is faster so), profiling and a
-// time limit (which look at single nests) and grids inside a batch (whose tables
-// hold the buffers) keep single iterations.
+// A tile the caller chose (or a searched one that is faster so), profiling (which
+// looks at single nests) and grids inside a batch (whose tables hold the buffers)
+// keep single iterations. A search's time limit does not: it has to time what the
+// run it chooses will do.
 }  // namespace
 
 bool grid_pair_eligible(ofl_grid *g, int iters) {
     if (launch_pair == nullptr || iters < 3 || g->mask != OFL_MASK_ALL_GPU || g->mode != OFL_XFER_HOISTED ||
-        g->profiling || g->deadline_ns != 0 || g->batch_refs != 0 || g->single_only || !grid_whole_nests(g))
+        g->profiling || g->batch_refs != 0 || g->single_only || !grid_whole_nests(g))
         return false;
     if (!g->pair_planned) {
         const int pitch = round_up(g->I, g->row_align > 0 ? g->row_align : kPitchAlign);
@@ -821,6 +822,8 @@ void run_pairs(ofl_grid *g, int from, int pairs, float omega) {
     grid_sync_wrk2_boundary(g);
     const bool graphed = g->fusion == 0 && static_cast<double>(g->n) <= kPairGraphPoints;
     for (int done = 0; done < pairs;) {
+        check_deadline(g);
+        g->pending = true;
         const int n = std::min(pairs - done, kGraphIters / 2);
         hipGraphExec_t exec = graphed ? loop_graph(g, 2 * n, omega, true) : nullptr;
         if (exec) {

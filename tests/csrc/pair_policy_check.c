@@ -1,7 +1,8 @@
 /* When iterations go in pairs, on the stand-in HIP runtime (hip_stand_in.cpp) with
  * launchers that count (pair_count.cpp): whatever was called before, a tile of the
  * caller's turns pairs off. A search measures tiles without them and leaves them on
- * unless it finds single iterations faster (the stand-in's times are all the same). */
+ * unless it finds single iterations faster (the stand-in's times are all the same).
+ * A search under a time limit runs what the run without one does, and stops. */
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -137,8 +138,24 @@ static int tuned(void) {
     return 0;
 }
 
+static int limited_search(void) {
+    problem pb;
+    ofl_loop_search_result r;
+    CHECK(make(&pb, 37, 19, 17) == OFL_OK);
+    const int wanted = 2 * 258 + 1 + 2 * 4;  /* two full graphs' worth of pairs and some */
+    const long n = pair_launches();
+    CHECK(ofl_grid_search_loops(pb.g, &kGa, wanted, 0.8f, OFL_XFER_HOISTED, 1e9, &r) == OFL_OK);
+    CHECK(pair_launches() > n && r.timed_out == 0);
+    /* every gene passes its limit at its first nest or its first pairs, but the
+     * all-CPU one, which is measured without a limit first and is no candidate */
+    CHECK(ofl_grid_search_loops(pb.g, &kGa, wanted, 0.8f, OFL_XFER_HOISTED, 1e-6, &r) == OFL_ESTATE);
+    CHECK(ofl_set_offload_mask(pb.g, OFL_MASK_ALL_GPU, OFL_XFER_HOISTED) == OFL_OK && grid_pairs(pb.g, 7) == 3);
+    drop(&pb);
+    return 0;
+}
+
 int main(void) {
-    if (batch_tiles() || grid_tiles() || tuned())
+    if (batch_tiles() || grid_tiles() || tuned() || limited_search())
         return 1;
     printf("pair policy ok\n");
     return 0;
