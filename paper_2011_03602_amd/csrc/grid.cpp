@@ -11,6 +11,7 @@
 #include <cmath>
 #include <utility>
 #include <cstring>
+#include <iterator>
 #include <limits>
 #include <memory>
 
@@ -719,17 +720,19 @@ void enqueue_iterations(ofl_grid *g, int iters, float omega) {
 // cannot be captured (for instance because the caller is capturing it). With
 // `pairs` they run in pairs (their shape follows from the grid).
 hipGraphExec_t loop_graph(ofl_grid *g, int iters, float omega, bool pairs = false) {
-    for (const auto &c : g->graphs)
+    for (auto &c : g->graphs)
         if (c.exec && c.iters == iters && c.omega == omega && c.whole_rows == g->wrk2_boundary_ok &&
-            c.pairs == pairs && same_tile(c.tile, g->tile) && same_view(c.view, g->view))
+            c.pairs == pairs && same_tile(c.tile, g->tile) && same_view(c.view, g->view)) {
+            c.used = ++g->graph_clock;
             return c.exec;
+        }
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(g->stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         return nullptr;
     }
-    auto &slot = g->graphs[g->graph_next];
-    g->graph_next ^= 1;
+    auto &slot = *std::min_element(std::begin(g->graphs), std::end(g->graphs),
+                                   [](const auto &a, const auto &b) { return a.used < b.used; });
     if (slot.exec) {
         hip_check(hipGraphExecDestroy(slot.exec), "hipGraphExecDestroy");
         slot.exec = nullptr;
@@ -753,6 +756,7 @@ hipGraphExec_t loop_graph(ofl_grid *g, int iters, float omega, bool pairs = fals
     (void)hipGraphDestroy(graph);
     hip_check(e, "hipGraphInstantiate");
     slot.exec = exec;
+    slot.used = ++g->graph_clock;
     slot.view = g->view;
     slot.tile = g->tile;
     slot.omega = omega;

@@ -79,7 +79,9 @@ struct ofl_grid {
     long long deadline_ns = 0;
 
     // Steady-state iterations replayed from captured HIP graphs (whole nests,
-    // hoisted, every nest on the GPU): two cached graphs, one per length.
+    // hoisted, every nest on the GPU): one cached graph per length and, where an odd
+    // number of pairs exchanges p and wrk2, per order of the two: a run of several
+    // lengths (a full graph and a shorter one) needs four in turn.
     struct LoopGraph {
         hipGraphExec_t exec = nullptr;
         ofl::GridView view{};
@@ -88,11 +90,13 @@ struct ofl_grid {
         int iters = 0;
         bool whole_rows = false;
         bool pairs = false;  // iterations in pairs (pair.hip)
+        unsigned long long used = 0;  // when it was last taken
     };
-    LoopGraph graphs[2];
+    static constexpr int kGraphs = 4;
+    LoopGraph graphs[kGraphs];
     ofl::PairShape pair;        // decomposition of iterations in pairs (vec 0: none)
     bool pair_planned = false;
-    int graph_next = 0;  // slot the next capture replaces
+    unsigned long long graph_clock = 0;  // counts takings; a capture replaces the longest unused
 
     bool broken = false;
     int batch_refs = 0;

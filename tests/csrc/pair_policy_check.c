@@ -2,7 +2,8 @@
  * launchers that count (pair_count.cpp): whatever was called before, a tile of the
  * caller's turns pairs off. A search measures tiles without them and leaves them on
  * unless it finds single iterations faster (the stand-in's times are all the same).
- * A search under a time limit runs what the run without one does, and stops. */
+ * A search under a time limit runs what the run without one does, and stops.
+ * Repeated runs replay their graphs. */
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -154,8 +155,29 @@ static int limited_search(void) {
     return 0;
 }
 
+/* Repeated runs replay their graphs: no capture, whatever the number of pairs. */
+static int replays(void) {
+    static const int iters[] = {8, 50, 100, 257, 258, 300, 303, 600, 1027};
+    problem pb;
+    CHECK(make(&pb, 37, 19, 17) == OFL_OK);
+    for (size_t t = 0; t < sizeof iters / sizeof *iters; ++t) {
+        CHECK(grid_pairs(pb.g, iters[t]) >= 0 && grid_pairs(pb.g, iters[t]) >= 0);
+        const long calls = stand_in_alloc_calls();
+        for (int r = 0; r < 4; ++r)
+            CHECK(grid_pairs(pb.g, iters[t]) == 0);
+        CHECK(stand_in_alloc_calls() == calls);
+    }
+    /* and so do two lengths in turn */
+    for (int r = 0; r < 2; ++r)
+        CHECK(grid_pairs(pb.g, 40) >= 0 && grid_pairs(pb.g, 60) >= 0);
+    for (int r = 0; r < 4; ++r)
+        CHECK(grid_pairs(pb.g, 40) == 0 && grid_pairs(pb.g, 60) == 0);
+    drop(&pb);
+    return 0;
+}
+
 int main(void) {
-    if (batch_tiles() || grid_tiles() || tuned() || limited_search())
+    if (batch_tiles() || grid_tiles() || tuned() || limited_search() || replays())
         return 1;
     printf("pair policy ok\n");
     return 0;
