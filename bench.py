@@ -947,7 +947,7 @@ def main():
         # the function-block routine (a matrix product on the matrix cores);
         # its parity against the FP64 oracle is a GPU test, not part of this line
         out["variants"]["gemm_f32"] = {"note": "ofl_gemm_f32: FP32 operands as exact sums of three bfloat16 parts at these "
-                                               "sizes, FP32 accumulation (so above the FP32 peak); parity: tests/test_gpu_gemm.py against the FP64 oracle_gemm",
+                                               "sizes, FP32 accumulation; parity: tests/test_gpu_gemm.py against the FP64 oracle_gemm",
                                        "shapes": []}
         for M, N, K in GEMM_SHAPES[:2]:
             sec = sorted(time_gemm(ofl, M, N, K) for _ in range(3))[1]  # median of three timings

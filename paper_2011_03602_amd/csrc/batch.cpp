@@ -230,7 +230,10 @@ namespace {
 // Items run in rounds of one work-group per CU, each chunk + 3 planes long (two
 // margin planes and the fill of the pipeline); the chunk is the one with the
 // fewest plane steps in all. Rows so long that their margins take more than 45%
-// of a work-group's points stay with single iterations, and so does a batch whose
+// of a work-group's points, for which the costs below were not fitted, stay with
+// single iterations (four grids of Ix65x65, 41 iterations in pairs against single
+// ones: I 300 1.2 against 3.1 ms, 440, the last that goes in pairs, 2.1 against 4.0,
+// 500 2.3 against 4.4, 700 4.9 against 5.9), and so does a batch whose
 // plane steps (us per plane as fitted for single grids at this width) would take
 // longer than two fused iterations at the copy rate. On 16 batches of 1 to 4
 // grids from 33x33x65 to 160x160x320 pairs were 2.1 to 6 times as fast as two

@@ -74,10 +74,12 @@ __device__ __forceinline__ int tile_index() {
 // behind the others' instructions.
 //
 // Bound by the loads of a tile's operands through L2, or by the latency of one
-// wave's share where there are few tiles. Measured, us against the former 64- or
-// 128-row by 256-column tiles: 8192 x 16 x 4096 22.1 against 566 (135 MB, 6.1
-// TB/s), 511 x 333 x 1001 with odd strides 9.6 against 183, 1000^3 30.6 against
-// 188, 128 x 128 x 4096 12.2 against 611, 64 x 4096 x 512 6.3 against 129.
+// wave's share where there are few tiles. Measured, us a launch among repeated ones
+// on the same operands, which the last-level cache then holds, against 64- or
+// 128-row by 256-column tiles: 8192 x 16 x 4096 22.1 against 566 (135 MB, 6.1 TB/s;
+// among calls on changing operands 30.0, 4.6 TB/s), 511 x 333 x 1001 with odd strides
+// 9.6 against 183 (calls: 10.7), 1000^3 30.6 against 188, 128 x 128 x 4096 12.2
+// against 611, 64 x 4096 x 512 6.3 against 129.
 template <int BASE>
 struct Mfma;
 template <>

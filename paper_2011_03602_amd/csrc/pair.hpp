@@ -59,7 +59,7 @@ struct PairForm {
     double plane_us;
 };
 inline double pair_us(const PairForm &form, long long blocks, int chunk, double rows, double bytes, int coef_elem) {
-    const long long slots = 256 * (form.vec == 4 ? 1 : 2);
+    const long long slots = 256 * (form.vec == 4 ? 1 : 2);  // an MI355X has 256 CUs, and the fit is theirs
     const double per_row = (coef_elem == 4 ? 1.18e-4 : 0.61e-4) * (bytes < 224.0 * (1 << 20) ? 1.0 : 2.0);
     double us = 3.0 + 0.004 * static_cast<double>(blocks);
     for (long long left = blocks; left > 0; left -= slots) {
@@ -139,7 +139,10 @@ inline int pair_flat_segments(int J, int pitch) {
 // 30.1; 161x161x321 85.0 -> 79.5 and 71.2 -> 62.8; 301x99x143 49.3 -> 46.7 and
 // 39.8 -> 36.4. Pairs are worth it while they take less than two single fused
 // iterations at the copy rate (a slab of one row, whose margins are five sixths
-// of the work, may not); 33x33x65 14.0 -> 3.1 us per iteration.
+// of the work, may not); 33x33x65 14.0 -> 3.1 us per iteration. Flat segments are
+// compared for rows whose margins leave half of them, and for grids that have a row
+// form: one without has none of few enough work-groups, or partial sums past its
+// staging buffer (thin grids of a few points), which segments share.
 inline bool pair_choose(int I, int J, int K, int pitch, int coef_elem, PairShape *best) {
     double us = 0.0;
     if (!pair_plan(I, J, K, pitch, coef_elem, best, &us))
