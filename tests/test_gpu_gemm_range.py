@@ -91,7 +91,7 @@ def timed(M, N, K, a, b):
         ev[1].record()
         torch.cuda.synchronize()
         ms.append(ev[0].elapsed_time(ev[1]))
-    return sorted(ms)[4]
+    return min(ms)
 
 
 @pytest.mark.parametrize("scale", [1e-18, 1e-30, 1e30])
