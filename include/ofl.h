@@ -551,20 +551,21 @@ int ofl_grid_search_loops(ofl_grid *g, const ofl_ga_params *ga, int iters, float
 /* Matrix product C = A B of row-major FP32 matrices in device memory: A is
  * M x K with row stride lda >= K, B is K x N with ldb >= N, C is M x N with
  * ldc >= N (strides in elements). C must not overlap A or B. The library's
- * matrix-core kernels are queued (small and narrow products: FP32 instructions;
- * large ones: each value as the exact sum of three bfloat16 parts, eight of the
- * nine part products, FP32 accumulation, with 128 x 128 tiles that meet infinities,
- * NaN, overflow, or values below 2^-103 beside values from 2^30 computed a second
- * time in FP32, which takes over three times as long). A sum of one product is
- * within 0.51 ulp; sums of products of normally distributed values have 0.2 to
- * 0.75 times the error of one FP32 sum over K (1 at K up to 32), sums that one
- * product dominates up to 1.1 times it. Infinities and NaN are as defined. The
- * launch is on stream (a
- * hipStream_t; NULL: the default stream) and the call returns without
- * waiting. Nothing is read or written when M or N is 0; K = 0 sets C to 0.
- * EINVAL for negative sizes, M above 65535 * 128, short strides, or a NULL
+ * matrix-core kernels are queued on stream (a hipStream_t; NULL: the default
+ * stream) and the call returns without waiting. Nothing is read or written when
+ * M or N is 0; K = 0 sets C to 0. EINVAL for negative sizes, M above 65535 * 128, short strides, or a NULL
  * pointer to an operand the product reads or writes; EDEVICE when the launch
- * fails. */
+ * fails.
+ * Small and narrow products run on FP32 instructions. Large ones take each value
+ * as the exact sum of three bfloat16 parts and eight of the nine part products,
+ * with FP32 accumulation: 128 x 128 tiles that meet infinities, NaN or overflow
+ * are then computed a second time in FP32, which takes over three times as long;
+ * so are those whose first 32 or 64 k hold a value from 2^30 while a nonzero one is
+ * below 2^-103, or hold none while a later value is from 2^104 or a sum from 2^82.
+ * Either way a sum of one product is within 0.51 ulp; sums of products of normally
+ * distributed values have 0.2 to 0.75 times the error of one FP32 sum over K (1 at
+ * K up to 32), sums that one product dominates up to 1.1 times it. Infinities and
+ * NaN are as defined. */
 int ofl_gemm_f32(int M, int N, int K, const float *A, int lda, const float *B, int ldb, float *C, int ldc,
                  void *stream);
 

@@ -248,7 +248,8 @@ __global__ __launch_bounds__(KS * 64) void gemm_direct_kernel(GemmArgs g, int ti
 // 2^-103, whose parts would be subnormal. A tile that meets one, or whose sums come
 // out infinite or NaN, is computed again with the FP32 instructions, straight from
 // global memory (4096^3 with every tile so: 3.4 ms): infinite and NaN operands,
-// overflow, and operands that mix those magnitudes. With operands always split as
+// overflow, and operands that mix those magnitudes or grow past the scaled range
+// only after the first stages. With operands always split as
 // they are and tiles redone below 2^-50, 4096^3 with one operand around 1e-18 took
 // 3355 us, since then what other operands take.
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
